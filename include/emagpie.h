@@ -22,12 +22,12 @@
  *    the host before anything is enqueued and leave all buffers untouched.
  *    emagpie_last_error(ctx) returns a message for the last failure of a
  *    call on that context (NULL: the last failure on the calling thread).
- *  - Device-side errors (a grid barrier of the persistent epoch that gave up
- *    waiting) are raised by the kernel into host-visible memory and returned
- *    as EMAGPIE_E_HIP by the first call on the context made after the failing
- *    work has completed (synchronise the stream to be sure of seeing it);
- *    that call does nothing else, and the state the failing epoch wrote is
- *    not valid.
+ *  - Device-side errors (workgroups of a persistent epoch or of a sequential
+ *    sweep that gave up waiting for each other) are raised by the kernel into
+ *    host-visible memory and returned as EMAGPIE_E_HIP by the first call on the
+ *    context made after the failing work has completed (synchronise the stream
+ *    to be sure of seeing it); that call does nothing else, and the state the
+ *    failing epoch wrote is not valid.
  *  - A context is not thread-safe; distinct contexts are independent.
  *  - Results are deterministic: the same inputs give bitwise-identical
  *    outputs (no floating-point atomics; every sum has a fixed order).
@@ -65,7 +65,7 @@ enum {
   EMAGPIE_PATH_AUTO = 4, /* chosen at init by timing FUSED and GRAPH epochs (and
                             CHAIN when minibatch = 1); PERSISTENT only on request: a
                             cooperative launch slows the process's later launches   */
-  EMAGPIE_PATH_CHAIN = 5 /* minibatch 1 only: one workgroup runs the whole sequential
+  EMAGPIE_PATH_CHAIN = 5 /* minibatch 1 only: one launch runs the whole sequential
                             sweep, each step applied in place (the paper's literal order,
                             Sec. 3 footnote: positions updated one after another)     */
 };
@@ -375,11 +375,11 @@ emagpie_status emagpie_misfit_noalloc(int32_t n_rows, int32_t n_cols, int32_t m,
                                       void* stream);
 
 /*
- * Fault-injection hook for the device-side error path of the persistent epoch
- * (tests only).  Later persistent epochs of ctx poll each grid barrier at most
+ * Fault-injection hook for the device-side error path of the persistent epoch and
+ * the sequential sweep (tests only).  Later ones of ctx poll in each wait at most
  * spin_limit times (0 restores the default, 2^25) and wait for target_skew more
- * arrivals than the grid makes, so with target_skew > 0 every barrier wait gives
- * up after spin_limit polls: the kernel still runs to its end (its results are
+ * arrivals than the grid makes, so with target_skew > 0 every wait between workgroups
+ * gives up after spin_limit polls: the kernel still runs to its end (its results are
  * then not valid) and raises the device error that the next call returns.
  * Host only.
  */

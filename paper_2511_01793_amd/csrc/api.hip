@@ -120,7 +120,7 @@ bool wants_tuning(const emagpie_config& c) {
 
 struct Layout {
   Region dperm, pos, slots, morder, tw32, tw64, numer, pnum, pden, pden_slot, phi, stack, zmax, ubuf, Dbuf,
-      scal, bar, phi_all, gz, gq, tune_obj, tune_probe, phase, part;
+      scal, bar, phi_all, gz, gq, tune_obj, tune_probe, phase, part, chain;
   int grad_chunk;
   size_t total;
 };
@@ -166,6 +166,8 @@ Layout make_layout(const emagpie_config& c) {
   L.phase = take(c.zero_phase_memory ? N * m2 * 8 : 0);
   // m = 256: strip maxima and column-block partial misfits per slot (16 of each)
   L.part = take(c.m == 256 ? B * 16 * (4 + 4 + 8) : 0);
+  // what a sequential sweep's workgroups exchange (minibatch 1)
+  L.chain = take(B == 1 ? emg::chain_scratch_bytes(c.m) : 0);
   L.total = cur;
   return L;
 }
@@ -295,8 +297,8 @@ emagpie_status use_ctx(emagpie_ctx c) {
     c->bar_ready = false;
     return fail(EMAGPIE_E_HIP,
                 "device error raised by earlier work on this context: a grid barrier of a persistent "
-                "epoch gave up waiting for the other workgroups; the object and probe that epoch "
-                "wrote are not valid");
+                "epoch, or a wait of a sequential sweep, gave up waiting for the other workgroups; the "
+                "object and probe that epoch wrote are not valid");
   }
   return EMAGPIE_OK;
 }
@@ -336,6 +338,11 @@ emg::StepArgs base_args(emagpie_ctx c, void* obj, void* probe) {
   a.ubuf = c->ubuf;
   a.qqmax = c->qqmax;
   return a;
+}
+
+emg::ChainSync chain_sync(emagpie_ctx c) {
+  return emg::ChainSync{reinterpret_cast<float2*>(c->ws + c->lay.chain.off), c->dev_err_dev,
+                        c->spin_limit, c->bar_skew};
 }
 
 // a (start, stop) event pair for timing category `cat`, or nulls when not timing
@@ -968,7 +975,8 @@ emagpie_status emagpie_step_minibatch(emagpie_ctx ctx, void* obj_dev, void* prob
   a.sampled = sampled_misfit_dev;
   if (ctx->cfg.path == EMAGPIE_PATH_CHAIN) {
     if (sampled_misfit_dev) EMG_HIP(emg::launch_zero_doubles(sampled_misfit_dev, 1, s));
-    EMG_HIP(emg::launch_chain_sweep(ctx->cfg.m, ctx->cfg.fft_plan, ctx->cfg.levels, a, b, s));
+    EMG_HIP(emg::launch_chain_sweep(ctx->cfg.m, ctx->cfg.fft_plan, ctx->cfg.levels, a, b,
+                                    chain_sync(ctx), s));
     return EMAGPIE_OK;
   }
   return enqueue_minibatch(ctx, a, ctx->cfg.path == EMAGPIE_PATH_PLAIN, s);
@@ -1037,7 +1045,8 @@ emagpie_status emagpie_epoch(emagpie_ctx ctx, void* obj_dev, void* probe_dev, in
       hipEvent_t e0, e1;
       EMG_OK(take_pair(ctx, 2, true, &e0, &e1));
       if (e0) EMG_HIP(hipEventRecord(e0, s));
-      EMG_HIP(emg::launch_chain_sweep(ctx->cfg.m, ctx->cfg.fft_plan, ctx->cfg.levels, a, N, s));
+      EMG_HIP(emg::launch_chain_sweep(ctx->cfg.m, ctx->cfg.fft_plan, ctx->cfg.levels, a, N,
+                                      chain_sync(ctx), s));
       if (e1) EMG_HIP(hipEventRecord(e1, s));
       return EMAGPIE_OK;
     }

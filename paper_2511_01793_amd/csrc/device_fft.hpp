@@ -96,29 +96,32 @@ __device__ __forceinline__ void dft4(cx<T>& a0, cx<T>& a1, cx<T>& a2, cx<T>& a3)
   a3 = sub(y1, y3);
 }
 
+// t[k] = W8^k o[k], k < 4
+template <typename T, bool INV>
+__device__ __forceinline__ void twiddle8(const cx<T>* o, cx<T>* t) {
+  const T h = T(0.70710678118654752440084436210484903928);
+  t[0] = o[0];
+  // W8^1 = (h, -h) forward, (h, +h) inverse
+  t[1] = INV ? cx<T>{h * (o[1].re - o[1].im), h * (o[1].re + o[1].im)}
+             : cx<T>{h * (o[1].re + o[1].im), h * (o[1].im - o[1].re)};
+  t[2] = rot90<T, INV>(o[2]);
+  // W8^3 = (-h, -h) forward, (-h, +h) inverse
+  t[3] = INV ? cx<T>{-h * (o[3].re + o[3].im), h * (o[3].re - o[3].im)}
+             : cx<T>{h * (o[3].im - o[3].re), -h * (o[3].re + o[3].im)};
+}
+
 template <typename T, bool INV>
 __device__ __forceinline__ void dft8(cx<T>* v) {
   // even / odd split: X_k = E_k + W8^k O_k, X_{k+4} = E_k - W8^k O_k
-  cx<T> e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6];
-  cx<T> o0 = v[1], o1 = v[3], o2 = v[5], o3 = v[7];
-  dft4<T, INV>(e0, e1, e2, e3);
-  dft4<T, INV>(o0, o1, o2, o3);
-  const T h = T(0.70710678118654752440084436210484903928);
-  // W8^1 = (h, -h) forward, (h, +h) inverse
-  cx<T> t1 = INV ? cx<T>{h * (o1.re - o1.im), h * (o1.re + o1.im)}
-                 : cx<T>{h * (o1.re + o1.im), h * (o1.im - o1.re)};
-  cx<T> t2 = rot90<T, INV>(o2);
-  // W8^3 = (-h, -h) forward, (-h, +h) inverse
-  cx<T> t3 = INV ? cx<T>{-h * (o3.re + o3.im), h * (o3.re - o3.im)}
-                 : cx<T>{h * (o3.im - o3.re), -h * (o3.re + o3.im)};
-  v[0] = add(e0, o0);
-  v[4] = sub(e0, o0);
-  v[1] = add(e1, t1);
-  v[5] = sub(e1, t1);
-  v[2] = add(e2, t2);
-  v[6] = sub(e2, t2);
-  v[3] = add(e3, t3);
-  v[7] = sub(e3, t3);
+  cx<T> e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]}, t[4];
+  dft4<T, INV>(e[0], e[1], e[2], e[3]);
+  dft4<T, INV>(o[0], o[1], o[2], o[3]);
+  twiddle8<T, INV>(o, t);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    v[k] = add(e[k], t[k]);
+    v[k + 4] = sub(e[k], t[k]);
+  }
 }
 
 // 16-point DFT as two 8-point halves: X_k = E_k + W16^k O_k, X_{k+8} = E_k - W16^k O_k,

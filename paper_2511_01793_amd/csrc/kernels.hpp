@@ -227,10 +227,11 @@ __device__ __forceinline__ void pix_rc(int tid, int e, int& r, int& c) {
 //   load(rd, r0, c0, q, z, R) fills the probe, object window and revised exit
 //   wave of the block at (r0, c0); element 2 i + j is pixel (r0 + i, c0 + j)
 // ---------------------------------------------------------------------------
-// DIRECT (minibatch of one slot, the whole step in one workgroup): instead of
-// storing numerators for the finalize, apply the finalize's arithmetic here --
-// sums that start from zero, z+ = N / D and Q+ = M / E, the joint step -- and write
-// the object window and the probe in place.  Every pixel has one owner thread.
+// A SINK takes the results.  ToSlots: the numerators go to the slot's buffers for the
+// finalize.  A direct sink (minibatch of one slot, each step applied in place): the
+// finalize's arithmetic runs here -- sums that start from zero, z+ = N / D and
+// Q+ = M / E, the joint step -- and the sink stores the new object and probe values.
+// Every pixel has one owner thread.
 // LY gives the thread's 2 x 2 blocks: LY::ROUNDS and LY::origin(tid, rd, r0, c0) in
 // patch coordinates, to which row0 is added (a strip of a larger patch).
 template <int M, int V>
@@ -248,10 +249,31 @@ struct PxLayout {
 constexpr float kMinDivisor = 1.17549435e-38f;  // FLT_MIN
 __device__ __forceinline__ float hw_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// ZP: the launch writes MAGPIE's z+ (a.zplus) instead of the numerators
-template <int M, class LY, int L, bool DIRECT, bool ZP, class LOAD>
+struct ToSlots {
+  static constexpr bool direct = false;
+};
+// object window of slot s and the probe in global memory
+template <int M>
+struct InPlace {
+  static constexpr bool direct = true;
+  const StepArgs& a;
+  int4 sl;
+  __device__ __forceinline__ void object(int r, int c, cx<float> v, bool changed) const {
+    if (changed) st(a.obj, (size_t)(sl.y + r) * a.n + sl.z + c, v);
+  }
+  __device__ __forceinline__ void probe(int r, int c, cx<float> v) const {
+    st(a.probe, (size_t)r * M + c, v);
+  }
+};
+
+// ZP: the launch writes MAGPIE's z+ (a.zplus) instead of the numerators.
+// PART: what a direct sink gets, kObject | kProbe (the two have separate results).
+constexpr int kObject = 1, kProbe = 2;
+template <int M, class LY, int L, bool ZP, int PART = kObject | kProbe, class SINK, class LOAD>
 __device__ __forceinline__ void pixel_update_body(const StepArgs& a, int s, int tid, int row0,
-                                                  LOAD& load, float qqmax, float zmax) {
+                                                  LOAD& load, float qqmax, float zmax,
+                                                  const SINK& sink) {
+  constexpr bool DIRECT = SINK::direct;
   const size_t base = (size_t)s * M * M;
   const bool slot_den = a.pden_slot != nullptr;
 #pragma unroll
@@ -314,21 +336,25 @@ __device__ __forceinline__ void pixel_update_body(const StepArgs& a, int s, int 
       }
     }
     if constexpr (DIRECT) {
-      const int4 sl = a.slot[s];
       const cx<float> zero{0.f, 0.f};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int r = r0 + (e >> 1), c = c0 + (e & 1);
-        const float dd = 0.f + D[e];
-        if (dd >= kMinDivisor) {
-          const cx<float> zp = scale(add(zero, N[e]), hw_rcp(dd));
-          st(a.obj, (size_t)(sl.y + r) * a.n + sl.z + c, a.joint ? aligned_sqrt(zz[e], zp) : zp);
+        if constexpr ((PART & kObject) != 0) {
+          const float dd = 0.f + D[e];
+          const bool changed = dd >= kMinDivisor;
+          cx<float> zn = zz[e];
+          if (changed) {
+            const cx<float> zp = scale(add(zero, N[e]), hw_rcp(dd));
+            zn = a.joint ? aligned_sqrt(zz[e], zp) : zp;
+          }
+          sink.object(r, c, zn, changed);
         }
-        if (a.update_probe) {
+        if ((PART & kProbe) != 0 && a.update_probe) {
           const float et = 0.f + (slot_den ? zmax : E[e]);
           if (et >= kMinDivisor) {
             const cx<float> qp = scale(add(zero, Mn[e]), hw_rcp(et));
-            st(a.probe, (size_t)r * M + c, a.joint ? aligned_sqrt(q[e], qp) : qp);
+            sink.probe(r, c, a.joint ? aligned_sqrt(q[e], qp) : qp);
           }
         }
       }
@@ -356,20 +382,24 @@ __device__ __forceinline__ void pixel_update_body(const StepArgs& a, int s, int 
 }
 
 // The z+ output is a uniform choice: each case has a copy of the loop, so neither
-// tests it per pixel (the minibatch-1 update of DIRECT never writes z+).
-template <int M, class LY, int L, bool DIRECT, class LOAD>
+// tests it per pixel (a direct sink never writes z+).
+template <int M, class LY, int L, class SINK, class LOAD>
 __device__ __forceinline__ void pixel_update_ly(const StepArgs& a, int s, int tid, int row0,
-                                                LOAD load, float qqmax, float zmax) {
-  if (!DIRECT && a.zplus)
-    pixel_update_body<M, LY, L, false, true>(a, s, tid, row0, load, qqmax, zmax);
+                                                LOAD load, float qqmax, float zmax,
+                                                const SINK& sink) {
+  if (!SINK::direct && a.zplus)
+    pixel_update_body<M, LY, L, true>(a, s, tid, row0, load, qqmax, zmax, ToSlots{});
   else
-    pixel_update_body<M, LY, L, DIRECT, false>(a, s, tid, row0, load, qqmax, zmax);
+    pixel_update_body<M, LY, L, false>(a, s, tid, row0, load, qqmax, zmax, sink);
 }
 
 template <int M, int V, int L, bool DIRECT = false, class LOAD>
 __device__ __forceinline__ void pixel_update(const StepArgs& a, int s, int tid, LOAD load,
                                              float qqmax, float zmax) {
-  pixel_update_ly<M, PxLayout<M, V>, L, DIRECT, LOAD>(a, s, tid, 0, load, qqmax, zmax);
+  if constexpr (DIRECT)
+    pixel_update_ly<M, PxLayout<M, V>, L>(a, s, tid, 0, load, qqmax, zmax, InPlace<M>{a, a.slot[s]});
+  else
+    pixel_update_ly<M, PxLayout<M, V>, L>(a, s, tid, 0, load, qqmax, zmax, ToSlots{});
 }
 
 // modulus projection of one pixel in transform order: Psi' = a Psi/|Psi|
@@ -1138,6 +1168,10 @@ __global__ __launch_bounds__((Plan<M, V>::NT)) void k_sweep_chain(StepArgs a, in
   }
   if (tid == 0 && a.sampled) *a.sampled = sampled;
 }
+
+}  // namespace emg
+#include "kernels_chain.hpp"
+namespace emg {
 
 // ---------------------------------------------------------------------------
 // plain path: one launch per stage, intermediates in HBM
@@ -1996,13 +2030,25 @@ hipError_t Launchers<M>::numerators(int v, int L, const StepArgs& a, hipStream_t
 }
 
 template <int M>
-hipError_t Launchers<M>::chain(int v, int L, const StepArgs& a, int n_steps, hipStream_t s) {
+hipError_t Launchers<M>::chain(int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
+                               hipStream_t s) {
   return with_plan<M>(v, [&](auto vc) {
     return with_levels(L, [&](auto lc) {
       return with_phase(a, [&](auto pc) {
         constexpr int V = decltype(vc)::value, LV = decltype(lc)::value;
-        hipLaunchKernelGGL((k_sweep_chain<M, V, LV, decltype(pc)::value>), dim3(1),
-                           dim3(Plan<M, V>::NT), 0, s, a, n_steps);
+        constexpr bool PH = decltype(pc)::value;
+        if constexpr (ChainMulti<M, V>::value) {
+          // no sequence number of an earlier launch may be found (a captured launch is
+          // replayed with the same numbers)
+          const hipError_t e = launch_fill_c64(y.scratch, 2 * chain_clear_units(M), make_float2(0.f, 0.f), s);
+          if (e != hipSuccess) return e;
+          const int parties = ChainMulti<M, V>::Workers + (a.sampled ? 1 : 0);
+          hipLaunchKernelGGL((k_chain_multi<M, V, LV, PH>), dim3(kDispatchXcds * (parties - 1) + 1),
+                             dim3(ChainMulti<M, V>::NT), 0, s, a, n_steps, y);
+        } else {
+          hipLaunchKernelGGL((k_sweep_chain<M, V, LV, PH>), dim3(1), dim3(Plan<M, V>::NT), 0, s, a,
+                             n_steps);
+        }
         return hipGetLastError();
       });
     });

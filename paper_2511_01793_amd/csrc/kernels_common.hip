@@ -137,8 +137,9 @@ hipError_t launch_numerators(int m, int v, int L, const StepArgs& a, hipStream_t
 hipError_t launch_surrogate_terms(int m, int v, const StepArgs& a, double* terms, hipStream_t s) {
   EMG_BY_M(m, surrogate(v, a, terms, s));
 }
-hipError_t launch_chain_sweep(int m, int v, int L, const StepArgs& a, int n_steps, hipStream_t s) {
-  EMG_BY_M(m, chain(v, L, a, n_steps, s));
+hipError_t launch_chain_sweep(int m, int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
+                              hipStream_t s) {
+  EMG_BY_M(m, chain(v, L, a, n_steps, y, s));
 }
 hipError_t launch_misfit_strips(int m, const StepArgs& a, int k0, int count, double* phi_out,
                                 hipStream_t s) {

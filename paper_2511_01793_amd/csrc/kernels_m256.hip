@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256) void k256_rows_inv(StepArgs a) {
   }
   const size_t n = (size_t)a.n;
   const float2* zwin = a.obj + (size_t)sl.y * n + sl.z;
-  pixel_update_ly<M, StripLayout, L, false>(
+  pixel_update_ly<M, StripLayout, L>(
       a, s, tid, row0,
       [&](int rd, int r0, int c0, cx<float>* q, cx<float>* zz, cx<float>* Rv) {
 #pragma unroll
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256) void k256_rows_inv(StepArgs a) {
           Rv[2 * i + 1] = A[(r0 - row0 + i) * LSR + c0 + 1];
         }
       },
-      qqmax, zmax);
+      qqmax, zmax, ToSlots{});
 }
 
 // per-pattern terms from the 16 partial sums of its column blocks (or strips), in
@@ -428,6 +428,8 @@ hipError_t Launchers256::revised_waves(int, const StepArgs&, hipStream_t) { retu
 hipError_t Launchers256::numerators(int, int, const StepArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t Launchers256::surrogate(int, const StepArgs&, double*, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t Launchers256::grad(int, bool, const GradArgs&, hipStream_t) { return hipErrorInvalidValue; }
-hipError_t Launchers256::chain(int, int, const StepArgs&, int, hipStream_t) { return hipErrorInvalidValue; }
+hipError_t Launchers256::chain(int, int, const StepArgs&, int, const ChainSync&, hipStream_t) {
+  return hipErrorInvalidValue;
+}
 
 }  // namespace emg

@@ -98,9 +98,30 @@ hipError_t launch_layout_intensities(int m, int v, const float* d, float* dperm,
 hipError_t launch_normalize_probe(int m, float2* probe, double dp_avg, int* zero_flag,
                                   hipStream_t s);
 
-// One workgroup runs a whole sequential sweep (minibatch 1): a.slot points at n_steps
+// what the workgroups of a sequential sweep exchange data through and wait for
+struct ChainSync {
+  float2* scratch;      // chain_scratch_bytes(m) bytes, 16-byte aligned
+  int* err;             // device-visible error flag, set when a wait gives up
+  unsigned spin_limit;  // polls of one wait before it gives up
+  unsigned skew;        // added to the sequence numbers awaited (fault injection; 0 in normal use)
+};
+// Scratch layout, in 16-byte units: two copies of the tile and the updated window, m^2
+// each; the maxima of every wave; the workgroups' XCDs; the counters; then (not cleared) the misfit terms of the
+// last kChainTermSteps steps, m^2 floats each.  None for the probe sides without it.
+constexpr int kChainTermSteps = 4;
+constexpr size_t chain_clear_units(int m) { return 3 * (size_t)m * m + 64 + 32 + 16; }
+inline size_t chain_scratch_bytes(int m) {
+  if (m != 64 && m != 128) return 0;
+  return chain_clear_units(m) * 16 + (size_t)kChainTermSteps * m * m * 4;
+}
+
+// One launch runs a whole sequential sweep (minibatch 1): a.slot points at n_steps
 // slots; each step's update is applied directly to the object window and the probe.
-hipError_t launch_chain_sweep(int m, int v, int L, const StepArgs& a, int n_steps, hipStream_t s);
+// Plans of 8- and 16-point passes at m = 64 and 128 run on several workgroups
+// (kernels_chain.hpp), which exchange data through y.scratch (cleared on the stream
+// first); the others on one.
+hipError_t launch_chain_sweep(int m, int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
+                              hipStream_t s);
 
 // misfit terms, unreduced: of all patterns (slot == nullptr; count = N, pattern k at
 // pos[k]) or of the count patterns of a slot list -> phi_out (count doubles): term j of
@@ -183,7 +204,8 @@ struct Launchers {
   static hipError_t numerators(int v, int L, const StepArgs& a, hipStream_t s);
   static hipError_t surrogate(int v, const StepArgs& a, double* terms, hipStream_t s);
   static hipError_t grad(int v, bool f64, const GradArgs& g, hipStream_t s);
-  static hipError_t chain(int v, int L, const StepArgs& a, int n_steps, hipStream_t s);
+  static hipError_t chain(int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
+                          hipStream_t s);
 };
 
 // m = 256 (kernels_m256.hip): the same members; the tile exceeds
@@ -214,7 +236,8 @@ struct Launchers256 {
   static hipError_t numerators(int v, int L, const StepArgs& a, hipStream_t s);
   static hipError_t surrogate(int v, const StepArgs& a, double* terms, hipStream_t s);
   static hipError_t grad(int v, bool f64, const GradArgs& g, hipStream_t s);
-  static hipError_t chain(int v, int L, const StepArgs& a, int n_steps, hipStream_t s);
+  static hipError_t chain(int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
+                          hipStream_t s);
   static hipError_t misfit_strips(const StepArgs& a, int k0, int count, double* phi_out,
                                   hipStream_t s);
 };

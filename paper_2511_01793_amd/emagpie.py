@@ -300,8 +300,8 @@ class Reconstruction:
         _check(lib().emagpie_phase_memory_reset(self._ctx, _stream()), self._ctx)
 
     def debug_barrier(self, spin_limit: int = 0, target_skew: int = 0):
-        """Fault injection for the persistent path's error reporting (tests only): grid
-        barriers of later persistent epochs poll at most spin_limit times (0: default) and
+        """Fault injection for the error reporting of persistent and chain epochs (tests only):
+        waits between workgroups of later ones poll at most spin_limit times (0: default) and
         wait for target_skew extra arrivals, so with target_skew > 0 every wait gives up and
         the next call raises E_HIP."""
         _check(lib().emagpie_debug_barrier(self._ctx, int(spin_limit), int(target_skew)), self._ctx)
