@@ -974,7 +974,6 @@ emagpie_status emagpie_step_minibatch(emagpie_ctx ctx, void* obj_dev, void* prob
   a.b = b;
   a.sampled = sampled_misfit_dev;
   if (ctx->cfg.path == EMAGPIE_PATH_CHAIN) {
-    if (sampled_misfit_dev) EMG_HIP(emg::launch_zero_doubles(sampled_misfit_dev, 1, s));
     EMG_HIP(emg::launch_chain_sweep(ctx->cfg.m, ctx->cfg.fft_plan, ctx->cfg.levels, a, b,
                                     chain_sync(ctx), s));
     return EMAGPIE_OK;
@@ -1037,7 +1036,6 @@ emagpie_status emagpie_epoch(emagpie_ctx ctx, void* obj_dev, void* probe_dev, in
       return EMAGPIE_OK;
     }
     case EMAGPIE_PATH_CHAIN: {
-      if (sampled_misfit_dev) EMG_HIP(emg::launch_zero_doubles(sampled_misfit_dev, 1, s));
       emg::StepArgs a = base_args(ctx, obj_dev, probe_dev);
       a.slot = ctx->slots;
       a.b = 1;

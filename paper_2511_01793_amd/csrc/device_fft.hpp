@@ -475,16 +475,40 @@ __device__ __forceinline__ void fft2_inverse(cx<T>* A, const cx<T>* tw, int tid)
 // y / (2t)), then the sign chosen so Re(root * conj(ref)) >= 0 (Eq. 6).  The
 // square roots and the reciprocal are the hardware's (within one ulp each).  A
 // product of modulus below 2^-125 (whose root is below 1.5e-19) gives 0; past that
-// test the second root and the reciprocal always take normal inputs.
+// test the second root and the reciprocal always take normal inputs.  Selects only: a
+// caller's pixels run beside each other (with a branch per pixel, four pixels of a thread
+// took their chains of roots and reciprocals one after another).
 __device__ __forceinline__ cx<float> aligned_sqrt(cx<float> ref, cx<float> plus) {
   const cx<float> w = mul(ref, plus);
   const float mag = __builtin_amdgcn_sqrtf(w.re * w.re + w.im * w.im);
-  if (mag < 2.35098870e-38f) return cx<float>{0.f, 0.f};
   const float t = __builtin_amdgcn_sqrtf((fabsf(w.re) + mag) * 0.5f);
   const float h = 0.5f * __builtin_amdgcn_rcpf(t);  // 1 / (2 t)
-  cx<float> s = w.re >= 0.f ? cx<float>{t, w.im * h} : cx<float>{fabsf(w.im) * h, copysignf(t, w.im)};
-  if (s.re * ref.re + s.im * ref.im < 0.f) s = cx<float>{-s.re, -s.im};
-  return s;
+  const bool right = w.re >= 0.f;
+  cx<float> s{right ? t : fabsf(w.im) * h, right ? w.im * h : copysignf(t, w.im)};
+  const bool flip = s.re * ref.re + s.im * ref.im < 0.f;
+  s = cx<float>{flip ? -s.re : s.re, flip ? -s.im : s.im};
+  const bool tiny = mag < 2.35098870e-38f;
+  return cx<float>{tiny ? 0.f : s.re, tiny ? 0.f : s.im};
+}
+
+// x[i] <- GM(x[i], plus[i]) or plus[i] (Eq. 6, or its rPIE form) where den[i] is large enough
+// to divide by, plus[i] = num[i] / den[i]; changed[i] says where
+template <int N>
+__device__ __forceinline__ void joint_step(cx<float>* x, const cx<float>* num, const float* den,
+                                           bool joint, float min_divisor, bool* changed) {
+  cx<float> p[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    changed[i] = den[i] >= min_divisor;
+    p[i] = scale(num[i], __builtin_amdgcn_rcpf(den[i]));
+  }
+  if (joint) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = aligned_sqrt(x[i], p[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    x[i] = cx<float>{changed[i] ? p[i].re : x[i].re, changed[i] ? p[i].im : x[i].im};
 }
 
 }  // namespace emg

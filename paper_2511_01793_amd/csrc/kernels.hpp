@@ -252,20 +252,6 @@ __device__ __forceinline__ float hw_rcp(float x) { return __builtin_amdgcn_rcpf(
 struct ToSlots {
   static constexpr bool direct = false;
 };
-// object window of slot s and the probe in global memory
-template <int M>
-struct InPlace {
-  static constexpr bool direct = true;
-  const StepArgs& a;
-  int4 sl;
-  __device__ __forceinline__ void object(int r, int c, cx<float> v, bool changed) const {
-    if (changed) st(a.obj, (size_t)(sl.y + r) * a.n + sl.z + c, v);
-  }
-  __device__ __forceinline__ void probe(int r, int c, cx<float> v) const {
-    st(a.probe, (size_t)r * M + c, v);
-  }
-};
-
 // ZP: the launch writes MAGPIE's z+ (a.zplus) instead of the numerators.
 // PART: what a direct sink gets, kObject | kProbe (the two have separate results).
 constexpr int kObject = 1, kProbe = 2;
@@ -336,27 +322,32 @@ __device__ __forceinline__ void pixel_update_body(const StepArgs& a, int s, int 
       }
     }
     if constexpr (DIRECT) {
+      // the finalize's sums of one slot, starting from zero
       const cx<float> zero{0.f, 0.f};
+      bool changed[4];
+      cx<float> num[4];
+      float den[4];
+      if constexpr ((PART & kObject) != 0) {
+        cx<float> zn[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = r0 + (e >> 1), c = c0 + (e & 1);
-        if constexpr ((PART & kObject) != 0) {
-          const float dd = 0.f + D[e];
-          const bool changed = dd >= kMinDivisor;
-          cx<float> zn = zz[e];
-          if (changed) {
-            const cx<float> zp = scale(add(zero, N[e]), hw_rcp(dd));
-            zn = a.joint ? aligned_sqrt(zz[e], zp) : zp;
-          }
-          sink.object(r, c, zn, changed);
+        for (int e = 0; e < 4; ++e) {
+          num[e] = add(zero, N[e]);
+          den[e] = 0.f + D[e];
+          zn[e] = zz[e];
         }
-        if ((PART & kProbe) != 0 && a.update_probe) {
-          const float et = 0.f + (slot_den ? zmax : E[e]);
-          if (et >= kMinDivisor) {
-            const cx<float> qp = scale(add(zero, Mn[e]), hw_rcp(et));
-            sink.probe(r, c, a.joint ? aligned_sqrt(q[e], qp) : qp);
-          }
+        joint_step<4>(zn, num, den, a.joint != 0, kMinDivisor, changed);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sink.object(r0 + (e >> 1), c0 + (e & 1), zn[e], changed[e]);
+      }
+      if ((PART & kProbe) != 0 && a.update_probe) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          num[e] = add(zero, Mn[e]);
+          den[e] = 0.f + (slot_den ? zmax : E[e]);
         }
+        joint_step<4>(q, num, den, a.joint != 0, kMinDivisor, changed);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sink.probe(r0 + (e >> 1), c0 + (e & 1), q[e]);
       }
       continue;
     }
@@ -382,24 +373,20 @@ __device__ __forceinline__ void pixel_update_body(const StepArgs& a, int s, int 
 }
 
 // The z+ output is a uniform choice: each case has a copy of the loop, so neither
-// tests it per pixel (a direct sink never writes z+).
-template <int M, class LY, int L, class SINK, class LOAD>
+// tests it per pixel.
+template <int M, class LY, int L, class LOAD>
 __device__ __forceinline__ void pixel_update_ly(const StepArgs& a, int s, int tid, int row0,
-                                                LOAD load, float qqmax, float zmax,
-                                                const SINK& sink) {
-  if (!SINK::direct && a.zplus)
+                                                LOAD load, float qqmax, float zmax) {
+  if (a.zplus)
     pixel_update_body<M, LY, L, true>(a, s, tid, row0, load, qqmax, zmax, ToSlots{});
   else
-    pixel_update_body<M, LY, L, false>(a, s, tid, row0, load, qqmax, zmax, sink);
+    pixel_update_body<M, LY, L, false>(a, s, tid, row0, load, qqmax, zmax, ToSlots{});
 }
 
-template <int M, int V, int L, bool DIRECT = false, class LOAD>
+template <int M, int V, int L, class LOAD>
 __device__ __forceinline__ void pixel_update(const StepArgs& a, int s, int tid, LOAD load,
                                              float qqmax, float zmax) {
-  if constexpr (DIRECT)
-    pixel_update_ly<M, PxLayout<M, V>, L>(a, s, tid, 0, load, qqmax, zmax, InPlace<M>{a, a.slot[s]});
-  else
-    pixel_update_ly<M, PxLayout<M, V>, L>(a, s, tid, 0, load, qqmax, zmax, ToSlots{});
+  pixel_update_ly<M, PxLayout<M, V>, L, LOAD>(a, s, tid, 0, load, qqmax, zmax);
 }
 
 // modulus projection of one pixel in transform order: Psi' = a Psi/|Psi|
@@ -497,7 +484,6 @@ __device__ __forceinline__ void xl_stage_amps(float* ampl, const float* ampv, in
 // ---------------------------------------------------------------------------
 // the whole patch stage for slot s, LDS-resident
 // ---------------------------------------------------------------------------
-// Returns the slot's sampled misfit (in thread 0).
 // STAGE: the twiddle table is loaded here (its load goes out beside the slot's,
 // its LDS copy is written before the first barrier) instead of by the caller.
 //
@@ -513,8 +499,8 @@ __device__ __forceinline__ void xl_stage_amps(float* ampl, const float* ampv, in
 //
 // PH = false: the context keeps no phase memory (a.phase is null), and the
 // projection is compiled without it; PH = true tests a.phase at run time.
-template <int M, int V, int L, bool DIRECT = false, bool STAGE = false, bool PH = true>
-__device__ __forceinline__ double patch_step(const StepArgs& a, int s, cx<float>* A,
+template <int M, int V, int L, bool STAGE = false, bool PH = true>
+__device__ __forceinline__ void patch_step(const StepArgs& a, int s, cx<float>* A,
                                            cx<float>* tws, float* redf, double* redd,
                                            int tid) {
   using P = Px<M, V>;
@@ -567,9 +553,9 @@ __device__ __forceinline__ double patch_step(const StepArgs& a, int s, cx<float>
     // is row i / R1, group g = i % R1, points g + R1 j: the loads of one j cover
     // 64 / R1 rows of a wave, R1 consecutive pixels of each.  The pass runs before the
     // first barrier: a launch that stages its twiddles here (STAGE) reads the pass's
-    // W^(g j) from the global table (cache-resident) with the other loads; the kernels
-    // that staged them in LDS once at their start (persistent, chain) read them there
-    // and hold fewer registers.
+    // W^(g j) from the global table (cache-resident) with the other loads; the
+    // persistent kernel, which staged them in LDS once at its start, reads them there
+    // and holds fewer registers.
     constexpr int R1 = Plan<M, V>::R1, R2 = Plan<M, V>::R2, DIT = M * R1 / NT;
     static_assert(DIT * NT == M * R1, "direct-gather items per thread");
     cx<float> ps[DIT][R2], twr[DIT][R2];
@@ -734,7 +720,7 @@ __device__ __forceinline__ double patch_step(const StepArgs& a, int s, cx<float>
   }
   float qqmax, zmax;
   lds_max2<NT>(redf, qqmax, zmax);
-  pixel_update<M, V, L, DIRECT>(
+  pixel_update<M, V, L>(
       a, s, tid,
       [&](int rd, int r0, int c0, cx<float>* q, cx<float>* zz, cx<float>* Rv) {
 #pragma unroll
@@ -754,13 +740,8 @@ __device__ __forceinline__ double patch_step(const StepArgs& a, int s, cx<float>
         }
       },
       qqmax, zmax);
-  double phi = 0.0;
-  if (tid == 0) {
-    phi = lds_sum<NT>(redd) / (2.0 * M * M);
-    if (a.phi) a.phi[s] = phi;
-  }
+  if (tid == 0 && a.phi) a.phi[s] = lds_sum<NT>(redd) / (2.0 * M * M);
   __syncthreads();  // LDS is reused by the next slot of a persistent loop
-  return phi;
 }
 
 // ---------------------------------------------------------------------------
@@ -908,15 +889,13 @@ __device__ __forceinline__ void finalize_item(const StepArgs& a, int item, int n
         }
       }
     }
+    bool changed[PER];
+    joint_step<PER>(zold, accn, accd, a.joint != 0, kMinDivisor, changed);
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
       const int q = tid + e * FNT;
       const int y = ty + q / T, x = tx + q % T;
-      if (accd[e] >= kMinDivisor && y < nr && x < n) {
-        const size_t o = (size_t)y * n + x;
-        const cx<float> zp = scale(accn[e], hw_rcp(accd[e]));
-        st(a.obj, o, a.joint ? aligned_sqrt(zold[e], zp) : zp);
-      }
+      if (changed[e] && y < nr && x < n) st(a.obj, (size_t)y * n + x, zold[e]);
     }
   } else {
     // probe unit: ppu pixels x G slot groups; group g sums slots [g per, (g + 1) per)
@@ -1016,7 +995,7 @@ __global__ __launch_bounds__((Plan<M, V>::NT)) void k_patch_step(const int4* slo
   __shared__ float redf[32];
   __shared__ double redd[16];
   const int tid = threadIdx.x;
-  patch_step<M, V, L, false, true, PH>(a, blockIdx.x, A, tws, redf, redd, tid);
+  patch_step<M, V, L, true, PH>(a, blockIdx.x, A, tws, redf, redd, tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -1035,7 +1014,7 @@ __global__ __launch_bounds__((Plan<M, V>::NT)) void k_patch_step_multi(const Ste
   const int tid = threadIdx.x;
   const int2 w = work[blockIdx.x];
   const StepArgs a = args[w.x];
-  patch_step<M, V, L, false, true, PH>(a, w.y, A, tws, redf, redd, tid);
+  patch_step<M, V, L, true, PH>(a, w.y, A, tws, redf, redd, tid);
 }
 
 template <int M, int F>
@@ -1129,7 +1108,7 @@ __global__ __launch_bounds__((Plan<M, V>::NT)) void k_epoch_persistent(StepArgs 
     x.slot = slots + start;
     x.b = min(B, n_pos - start);
     for (int s = blockIdx.x; s < x.b; s += gridDim.x)
-      patch_step<M, V, L, false, false, PH>(x, s, A, tws, redf, redd, tid);
+      patch_step<M, V, L, false, PH>(x, s, A, tws, redf, redd, tid);
     target += gridDim.x;
     grid_barrier(bar, target, err, spin_limit);
     for (int item = blockIdx.x; item < nitems; item += gridDim.x)
@@ -1137,36 +1116,6 @@ __global__ __launch_bounds__((Plan<M, V>::NT)) void k_epoch_persistent(StepArgs 
     target += gridDim.x;
     grid_barrier(bar, target, err, spin_limit);
   }
-}
-
-// Sequential sweep of minibatch-1 steps in one workgroup (the paper's literal
-// order: each step sees the previous step's object and probe).  No grid-wide
-// synchronisation: every step touches only its own window and the probe, and the
-// workgroup barrier at the end of each step orders it before the next.  The
-// sampled misfit accumulates exactly as the finalize adds it.
-template <int M, int V, int L, bool PH>
-__global__ __launch_bounds__((Plan<M, V>::NT)) void k_sweep_chain(StepArgs a, int n_steps) {
-  __shared__ cx<float> A[M * lds_stride<M>()];
-  __shared__ cx<float> tws[M];
-  __shared__ float redf[32];
-  __shared__ double redd[16];
-  const int tid = threadIdx.x;
-  stage_twiddles<M, Plan<M, V>::NT>(a.tw, tws, tid);
-  __syncthreads();
-  const int4* slots = a.slot;
-  // the running sum stays in a register of thread 0 (the finalize's order:
-  // sampled <- sampled + (0 + phi) after every step), stored once at the end
-  double sampled = (tid == 0 && a.sampled) ? *a.sampled : 0.0;
-  for (int step = 0; step < n_steps; ++step) {
-    StepArgs x = a;
-    x.slot = slots + step;
-    x.b = 1;
-    const double phi = patch_step<M, V, L, true, false, PH>(x, 0, A, tws, redf, redd, tid);
-    double t = 0.0;
-    t += phi;
-    sampled += t;
-  }
-  if (tid == 0 && a.sampled) *a.sampled = sampled;
 }
 
 }  // namespace emg
@@ -2037,18 +1986,11 @@ hipError_t Launchers<M>::chain(int v, int L, const StepArgs& a, int n_steps, con
       return with_phase(a, [&](auto pc) {
         constexpr int V = decltype(vc)::value, LV = decltype(lc)::value;
         constexpr bool PH = decltype(pc)::value;
-        if constexpr (ChainMulti<M, V>::value) {
-          // no sequence number of an earlier launch may be found (a captured launch is
-          // replayed with the same numbers)
-          const hipError_t e = launch_fill_c64(y.scratch, 2 * chain_clear_units(M), make_float2(0.f, 0.f), s);
-          if (e != hipSuccess) return e;
-          const int parties = ChainMulti<M, V>::Workers + (a.sampled ? 1 : 0);
-          hipLaunchKernelGGL((k_chain_multi<M, V, LV, PH>), dim3(kDispatchXcds * (parties - 1) + 1),
-                             dim3(ChainMulti<M, V>::NT), 0, s, a, n_steps, y);
-        } else {
-          hipLaunchKernelGGL((k_sweep_chain<M, V, LV, PH>), dim3(1), dim3(Plan<M, V>::NT), 0, s, a,
-                             n_steps);
-        }
+        const hipError_t e = launch_chain_clear(M, y.scratch, a.sampled, s);
+        if (e != hipSuccess) return e;
+        const int parties = Chain<M, V>::Workers + (a.sampled ? 1 : 0);
+        hipLaunchKernelGGL((k_chain<M, V, LV, PH>), dim3(kDispatchXcds * (parties - 1) + 1),
+                           dim3(Chain<M, V>::NT), 0, s, a, n_steps, y);
         return hipGetLastError();
       });
     });

@@ -1,11 +1,10 @@
 // The sequential sweep (minibatch 1: the paper's literal order) of one patch spread over
 // several workgroups, one launch for the whole sweep.
 //
-// A step is a dependent chain of transforms of one m x m patch.  One workgroup (the
-// chain of kernels.hpp) does all of its arithmetic on one CU, which took 29.4 us per step
-// at m = 128 and 8.1 us at m = 64 (that CU's VALU, then LDS and load latency).  Here m^2 / 1024
-// workgroups of 256 threads share a step, each owning LINES rows of the patch and LINES
-// columns of the spectrum, 4 points per thread.  Per step:
+// A step is a dependent chain of transforms of one m x m patch.  One workgroup per step
+// took 29.4 us at m = 128 and 8.1 us at m = 64 (one CU's VALU, then LDS and load latency).
+// Here m^2 / 1024 workgroups of 256 threads share a step, each owning LINES rows of the
+// patch and LINES columns of the spectrum, 4 points per thread.  Per step:
 //   1. row phase: exit wave psi = Q . z_k and the forward row passes;
 //   2. column phase: forward column passes, modulus projection, inverse column passes;
 //   3. row phase: inverse row passes, the per-pixel update, the new object window.
@@ -38,14 +37,16 @@
 namespace emg {
 
 template <int M, int V>
-struct ChainMulti {
+struct Chain {
   static constexpr int R1 = Plan<M, V>::R1, R2 = Plan<M, V>::R2;
-  // 8- and 16-point passes; m = 32 is one workgroup's work, without any exchange
-  static constexpr bool value = M >= 64 && (R1 == 8 || R1 == 16) && (R2 == 8 || R2 == 16);
   static constexpr int NT = 256, WAVES = NT / 64;
   static constexpr int LINES = 4 * NT / M;  // rows, and columns, of a workgroup
   static constexpr int Workers = M / LINES;
-  static constexpr int LS = M + 2;  // LDS row stride: at most two-way bank conflicts in any pass
+  // m = 32 is one workgroup's work: the tile stays in its LDS, where the other sides' columns
+  // and window travel as packets
+  static constexpr bool SOLO = Workers == 1;
+  // LDS row stride: at most two-way bank conflicts in any pass (m = 32: four-way in one)
+  static constexpr int LS = SOLO ? M + 4 : M + 2;
   // order of a block's LINES columns in the exchanged tile: where a lane pair holds two
   // neighbouring points of two groups (8-point runs, 16 lines), those four lie together
   __device__ static int slot(int c) {
@@ -123,8 +124,8 @@ __device__ __forceinline__ cx<float> ld_agent(__amdgpu_buffer_rsrc_t r, int i) {
   return cx<float>{__int_as_float(v[0]), __int_as_float(v[1])};
 }
 
-// One pass of R points over the workgroup's 1024, 4 points per thread: a DFT takes R / 4
-// lanes of a wave, which differ in lane bit 4 (h0) and, for R = 16, bit 5 (h1).  The even
+// One pass of R points (4, 8 or 16) over the workgroup's 1024, 4 points per thread: a DFT
+// takes R / 4 lanes of a wave, which differ in lane bit 4 (h0) and, for R = 16, bit 5 (h1).  The even
 // inputs lie in the lanes with one of these bits clear, so each lane runs the 4-point DFTs and
 // twiddles of dft8 / dft16 on its own inputs, and each butterfly across lanes is one lane
 // swap and one fused add (the same operations on the same operands as dft8 / dft16).
@@ -136,17 +137,18 @@ struct PassPlace {
 // input and output index of a thread's value i in its DFT
 template <int R, int F = 0>
 __device__ __forceinline__ int pass_in(int i, const PassPlace& p) {
-  return R == 8 ? 2 * i + p.h0 : F == 0 ? 4 * i + 2 * p.h0 + p.h1 : 4 * i + 2 * p.h1 + p.h0;
+  return R == 4 ? i : R == 8 ? 2 * i + p.h0 : F == 0 ? 4 * i + 2 * p.h0 + p.h1 : 4 * i + 2 * p.h1 + p.h0;
 }
 template <int R, int F = 0>
 __device__ __forceinline__ int pass_out(int i, const PassPlace& p) {
-  return R == 8 ? 4 * p.h0 + i : F == 0 ? 8 * p.h1 + 4 * p.h0 + i : 8 * p.h0 + 4 * p.h1 + i;
+  return R == 4 ? i : R == 8 ? 4 * p.h0 + i : F == 0 ? 8 * p.h1 + 4 * p.h0 + i : 8 * p.h0 + 4 * p.h1 + i;
 }
 // the thread's part of an item, and its item of the pass
 template <int R>
 __device__ __forceinline__ int pass_item(int t, PassPlace& p) {
-  p.h0 = (t >> 4) & 1;
+  p.h0 = R >= 8 ? (t >> 4) & 1 : 0;
   p.h1 = R == 16 ? (t >> 5) & 1 : 0;
+  if (R == 4) return t;
   return (t & 15) | (R == 16 ? (t >> 6) << 4 : (t >> 5) << 4);
 }
 
@@ -167,6 +169,7 @@ template <int R, bool INV, int F = 0>
 __device__ __forceinline__ void group_dft(cx<float>* v, const PassPlace& p) {
   const bool second = R == 8 || F == 0 ? p.h0 != 0 : p.h1 != 0;
   dft4<float, INV>(v[0], v[1], v[2], v[3]);
+  if constexpr (R == 4) return;
   cx<float> t[4];
   twiddle8<float, INV>(v, t);
   cross_butterfly<(R == 8 || F == 0) ? 16 : 32>(v, t, second);
@@ -192,6 +195,7 @@ __device__ __forceinline__ void group_dft(cx<float>* v, const PassPlace& p) {
 // and register bits exchanged
 template <int R>
 __device__ __forceinline__ void outputs_to_inputs(cx<float>* v) {
+  if constexpr (R == 4) return;
   xl_exchange<16>(v[0], v[1]);
   xl_exchange<16>(v[2], v[3]);
   if constexpr (R == 16) {
@@ -215,19 +219,20 @@ struct ChainRows {
   }
 };
 
-// New window values to the object and, as packets, to the other workgroups; new probe values
-// to the rows in LDS.
-template <int M, int LS>
+// New window values to the object and to the next step (as packets, or in the one workgroup's
+// LDS); new probe values to the rows in LDS.
+template <int M, int LS, bool SOLO>
 struct ChainSink {
   static constexpr bool direct = true;
   __amdgpu_buffer_rsrc_t win, packets;
   int n, row0;
   unsigned number;
   bool shared_l2;
-  cx<float>* q;
+  cx<float>*q, *z;
   __device__ __forceinline__ void object(int r, int c, cx<float> v, bool changed) const {
     const int at = r * M + c;
-    send<1>(packets, &at, &v, number, shared_l2);
+    if constexpr (SOLO) z[r * LS + c] = v;
+    else send<1>(packets, &at, &v, number, shared_l2);
     if (changed) st_through(win, r * n + c, v);
   }
   __device__ __forceinline__ void probe(int r, int c, cx<float> v) const { q[(r - row0) * LS + c] = v; }
@@ -246,7 +251,7 @@ constexpr int kChainStored = 0, kChainSummed = 32;
 template <int M, int V>
 __device__ __forceinline__ void chain_account(const StepArgs& a, int n_steps, float* terms,
                                               unsigned* counters, const ChainWait& wait, unsigned skew) {
-  using C = ChainMulti<M, V>;
+  using C = Chain<M, V>;
   using CP = ColPass<M, V>;
   constexpr int NTV = Plan<M, V>::NT, IT = NTV / C::NT;
   static_assert(IT * C::NT == NTV, "the plan's threads in whole rounds");
@@ -304,13 +309,15 @@ __device__ __forceinline__ void chain_account(const StepArgs& a, int n_steps, fl
 }
 
 template <int M, int V, int L, bool PH>
-__global__ __launch_bounds__((ChainMulti<M, V>::NT)) void k_chain_multi(StepArgs a, int n_steps,
+__global__ __launch_bounds__((Chain<M, V>::NT)) void k_chain(StepArgs a, int n_steps,
                                                                       ChainSync y) {
-  using C = ChainMulti<M, V>;
+  using C = Chain<M, V>;
   constexpr int R1 = C::R1, R2 = C::R2, LINES = C::LINES, LS = C::LS, NT = C::NT;
   constexpr int WAVES = C::WAVES * C::Workers;
   static_assert(WAVES <= 64, "one packet of maxima per lane");
-  __shared__ alignas(16) cx<float> Q[LINES * LS], Z[LINES * LS], W[LINES * LS];
+  constexpr bool SOLO = C::SOLO;
+  __shared__ alignas(16) cx<float> Q[LINES * LS], Z2[(SOLO ? 2 : 1) * LINES * LS], W[LINES * LS];
+  __shared__ float redf[2 * NT / 64];
   __shared__ int dead;
   if (blockIdx.x % kDispatchXcds != 0) return;
   const int tid = threadIdx.x, ln = tid & 63, party = blockIdx.x / kDispatchXcds;
@@ -328,20 +335,23 @@ __global__ __launch_bounds__((ChainMulti<M, V>::NT)) void k_chain_multi(StepArgs
     return;
   }
   const __amdgpu_buffer_rsrc_t b1 = through_buffer(tile1, 2 * M * M), b2 = through_buffer(tile2, 2 * M * M),
-                               bw = through_buffer(window, 2 * M * M), bm = through_buffer(maxima, 2 * 64), bx = through_buffer(maxima + 2 * 64, 2 * 32);
+                               bw = through_buffer(window, 2 * M * M), bm = through_buffer(maxima, 2 * 64), bx = through_buffer(maxima + 2 * 64, 2 * 32),
+                               cb = through_buffer(reinterpret_cast<float2*>(counters), 32);
   const int line0 = party * LINES;  // its rows, and columns
   // places in the passes.  Strided row passes: lanes of a row beside each other (window
   // rows are read that way).  The others: lanes of one position beside each other (the
-  // order of the exchanged tile and of the intensities).
+  // order of the exchanged tile and of the intensities).  The one workgroup of m = 32: every
+  // pass with whole lines in a wave, so that only the turns between rows and columns and
+  // the new window need a block barrier.
   PassPlace sr, sc, ct;
   const int ir = pass_item<R2>(tid, sr), ic = pass_item<R1>(tid, ct);
   sc = sr;
   sr.line = ir / R1;
   sr.g = ir % R1;
-  sc.line = C::column(ir % LINES);
-  sc.g = ir / LINES;
-  ct.line = ic % LINES;
-  ct.g = ic / LINES;
+  sc.line = SOLO ? ir / R1 : C::column(ir % LINES);
+  sc.g = SOLO ? ir % R1 : ir / LINES;
+  ct.line = SOLO ? ic / R2 : ic % LINES;
+  ct.g = SOLO ? ic % R2 : ic / LINES;
   // packet of the tile's element (row, p): blocks of LINES transform-order columns
   auto at = [](int row, int p) { return ((p / LINES) * M + row) * LINES + C::slot(p % LINES); };
   int at_row[4], at_col_in[4], at_col_out[4], at_row_in[4];
@@ -372,23 +382,33 @@ __global__ __launch_bounds__((ChainMulti<M, V>::NT)) void k_chain_multi(StepArgs
     for (int i = 1; i < 4; ++i) v[i] = mul_fma(w[i], v[i]);
   };
   // the values of a pass in W: points g + R1 j (strided) or R1 g + j (contiguous) of a
-  // line.  An item's lanes lie in one wave, so an item goes back to where it was read
+  // line, a column's in a row of W of their own or (the one workgroup) down W.  An item's lanes lie in one wave, so an item goes back to where it was read
   // without a block barrier; wave_order keeps the compiler from moving the accesses.
   auto wave_order = []() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
-  auto put_strided = [&](const cx<float>* v, const PassPlace& s) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) W[s.line * LS + s.g + R1 * pass_out<R2>(i, s)] = v[i];
+  auto line_sync = [&]() {
+    if constexpr (SOLO) wave_order();
+    else __syncthreads();
   };
-  auto get_strided = [&](cx<float>* v, const PassPlace& s) {
+  auto in_row = [](int line, int p) { return line * LS + p; };
+  auto in_column = [](int line, int p) { return SOLO ? p * LS + line : line * LS + p; };
+  auto put_strided = [&](auto in, const cx<float>* v, const PassPlace& s) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = W[s.line * LS + s.g + R1 * pass_in<R2>(i, s)];
+    for (int i = 0; i < 4; ++i) W[in(s.line, s.g + R1 * pass_out<R2>(i, s))] = v[i];
   };
-  auto get_contiguous = [&](cx<float>* v) {
+  auto get_strided = [&](auto in, cx<float>* v, const PassPlace& s) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = W[ct.line * LS + R1 * ct.g + pass_in<R1>(i, ct)];
+    for (int i = 0; i < 4; ++i) v[i] = W[in(s.line, s.g + R1 * pass_in<R2>(i, s))];
+  };
+  auto put_contiguous = [&](auto in, const cx<float>* v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) W[in(ct.line, R1 * ct.g + pass_out<R1>(i, ct))] = v[i];
+  };
+  auto get_contiguous = [&](auto in, cx<float>* v) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = W[in(ct.line, R1 * ct.g + pass_in<R1>(i, ct))];
   };
 
   for (int e = tid; e < LINES * M; e += NT) Q[(e / M) * LS + e % M] = ld(a.probe, (size_t)line0 * M + e);
@@ -414,14 +434,15 @@ __global__ __launch_bounds__((ChainMulti<M, V>::NT)) void k_chain_multi(StepArgs
     for (int i = 0; i < 4; ++i)
       z[i] = ld_agent(w, (line0 + sr.line) * a.n + sr.g + R1 * pass_in<R2>(i, sr));
   };
-  int4 sl = uniform(a.slot[0]), before = sl;
+  // slots run a step ahead of the window they give: no step waits for its slot's load
+  int4 sl = uniform(a.slot[0]), before = sl, ahead = a.slot[min(1, n_steps - 1)];
   cx<float> z[4];
   load_window(sl, z);
   load_intensities(sl.x);
   __syncthreads();
   // are all workgroups on one XCD?  Each tells its XCD's number and looks at every other's.
-  bool shared_l2;
-  {
+  bool shared_l2 = false;
+  if constexpr (!SOLO) {
     const float xcd = (float)(__builtin_amdgcn_s_getreg(kHwRegXccId) & 15u);
     const int to = party, from = ln % C::Workers;
     cx<float> m{xcd, 0.f};
@@ -432,7 +453,9 @@ __global__ __launch_bounds__((ChainMulti<M, V>::NT)) void k_chain_multi(StepArgs
 
   for (int step = 0; step < n_steps; ++step) {
     const unsigned sent = (unsigned)step + 1, n = sent + y.skew;  // packets' numbers: sent, awaited
-    const int4 next = uniform(a.slot[min(step + 1, n_steps - 1)]);
+    const int4 next = uniform(ahead);
+    ahead = a.slot[min(step + 2, n_steps - 1)];
+    cx<float>* Z = Z2 + (SOLO && (step & 1) ? LINES * LS : 0);
     cx<float> v[4];
     float d[4];
 #pragma unroll
@@ -448,9 +471,19 @@ __global__ __launch_bounds__((ChainMulti<M, V>::NT)) void k_chain_multi(StepArgs
         for (int i = 0; i < 4; ++i) {
           const int c = sr.g + R1 * pass_in<R2>(i, sr) + dc;
           in[i] = (unsigned)dr < (unsigned)M && (unsigned)c < (unsigned)M;
-          from[i] = in[i] ? dr * M + c : 0;
+          from[i] = in[i] ? dr * (SOLO ? LS : M) + c : 0;
         }
-        if (in[0] || in[1] || in[2] || in[3]) receive<4>(bw, from, in, z, n - 1, wait);
+        if constexpr (SOLO) {
+          const cx<float>* Zp = Z2 + (step & 1 ? 0 : LINES * LS);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            cx<float> t = Zp[from[i]];
+            asm("" : "+v"(t.re), "+v"(t.im));  // loaded by every lane, not behind a branch
+            z[i] = cx<float>{in[i] ? t.re : z[i].re, in[i] ? t.im : z[i].im};
+          }
+        } else if (in[0] || in[1] || in[2] || in[3]) {
+          receive<4>(bw, from, in, z, n - 1, wait);
+        }
       }
       float q2m = 0.f, z2m = 0.f;
 #pragma unroll
@@ -465,30 +498,48 @@ __global__ __launch_bounds__((ChainMulti<M, V>::NT)) void k_chain_multi(StepArgs
       load_intensities(next.x);
       group_dft<R2, false>(v, sr);
       twiddle(v, wrf);
-      put_strided(v, sr);
-      __syncthreads();
-      get_contiguous(v);
+      put_strided(in_row, v, sr);
+      if constexpr (SOLO) wave_max2_to_lds<NT>(q2m, z2m, redf, tid);
+      line_sync();
+      get_contiguous(in_row, v);
       group_dft<R1, false>(v, ct);
-      outputs_to_inputs<R1>(v);
-      send<4>(b1, at_row, v, sent, shared_l2);
-      q2m = wave_max(q2m);
-      z2m = wave_max(z2m);
-      if (ln == 0) {
-        const int to = party * C::WAVES + (tid >> 6);
-        const cx<float> m{q2m, z2m};
-        send<1>(bm, &to, &m, sent, shared_l2);
+      if constexpr (SOLO) {
+        wave_order();
+        put_contiguous(in_row, v);
+      } else {
+        outputs_to_inputs<R1>(v);
+        send<4>(b1, at_row, v, sent, shared_l2);
+        q2m = wave_max(q2m);
+        z2m = wave_max(z2m);
+        if (ln == 0) {
+          const int to = party * C::WAVES + (tid >> 6);
+          const cx<float> m{q2m, z2m};
+          send<1>(bm, &to, &m, sent, shared_l2);
+        }
       }
     }
 
     // 2. forward column passes, projection, inverse column passes
+    // a look at the summing workgroup's progress (in a vector register, so it is not waited for
+    // before its use)
+    int summed = 0, lane0 = 0;
+    asm("" : "+v"(lane0));
+    if (a.sampled)
+      summed = __builtin_amdgcn_raw_buffer_load_b32(cb, lane0 + kChainSummed * 4, 0, kCachePolicyThrough);
     float t[4];
     cx<float> pm{0.f, 0.f};
-    receive<4>(b1, at_col_in, every, v, n, wait);
+    if constexpr (SOLO) {
+      __syncthreads();
+      get_strided(in_column, v, sc);
+    } else {
+      receive<4>(b1, at_col_in, every, v, n, wait);
+    }
     group_dft<R2, false>(v, sc);
     twiddle(v, wcf);
-    __syncthreads();  // every wave has read its row items
-    put_strided(v, sc);
-    {
+    if constexpr (SOLO) wave_order();
+    else __syncthreads();  // every wave has read its row items
+    put_strided(in_column, v, sc);
+    if constexpr (!SOLO) {
       const int from = ln % WAVES;
       receive<1>(bm, &from, every, &pm, n, wait);
     }
@@ -500,7 +551,7 @@ __global__ __launch_bounds__((ChainMulti<M, V>::NT)) void k_chain_multi(StepArgs
     if (dead) break;
     if (a.sampled && tid == 0 && step > 0)
       __hip_atomic_fetch_add(counters + kChainStored, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    get_contiguous(v);
+    get_contiguous(in_column, v);
     group_dft<R1, false>(v, ct);
     {
       float2* ph =
@@ -513,35 +564,49 @@ __global__ __launch_bounds__((ChainMulti<M, V>::NT)) void k_chain_multi(StepArgs
     group_dft<R1, true, 1>(v, ct);
     wave_order();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) W[ct.line * LS + R1 * ct.g + pass_out<R1, 1>(i, ct)] = v[i];
-    __syncthreads();
-    get_strided(v, sc);
+    for (int i = 0; i < 4; ++i) W[in_column(ct.line, R1 * ct.g + pass_out<R1, 1>(i, ct))] = v[i];
+    line_sync();
+    get_strided(in_column, v, sc);
     twiddle(v, wci);
     group_dft<R2, true>(v, sc);
-    send<4>(b2, at_col_out, v, sent, shared_l2);
+    if constexpr (SOLO) {
+      wave_order();
+      put_strided(in_column, v, sc);
+    } else {
+      send<4>(b2, at_col_out, v, sent, shared_l2);
+    }
     if (a.sampled) {
-      if (step >= kChainTermSteps)
-        wait.counter(counters + kChainSummed, (unsigned)(step + 1 - kChainTermSteps) + y.skew);
+      if (step >= kChainTermSteps && (int)((unsigned)summed + kChainTermSteps - n) < 0)
+        wait.counter(counters + kChainSummed, n - kChainTermSteps);
       st_pair_through(through_buffer(reinterpret_cast<float2*>(
                                          terms + (size_t)(step % kChainTermSteps) * M * M), M * M / 2),
                       (tline * M + trow) / 2, cx<float>{t[0], t[1]}, cx<float>{t[2], t[3]});
     }
 
     // 3. inverse row passes, then the update of the workgroup's rows
-    receive<4>(b2, at_row_in, every, v, n, wait);
-    group_dft<R1, true>(v, ct);
-    const float qqmax = wave_max(pm.re), zmax = wave_max(pm.im);
-    __syncthreads();  // every wave has read its column items, and received: from all workgroups
+    float qqmax, zmax;
+    if constexpr (SOLO) {
+      __syncthreads();
+      get_contiguous(in_row, v);
+      group_dft<R1, true>(v, ct);
+      lds_max2<NT>(redf, qqmax, zmax);
+      wave_order();
+    } else {
+      qqmax = wave_max(pm.re);
+      zmax = wave_max(pm.im);
+      receive<4>(b2, at_row_in, every, v, n, wait);
+      group_dft<R1, true>(v, ct);
+      __syncthreads();  // every wave has read its column items, and received: from all workgroups
+    }
     load_window(next, z);  // current outside this step's window
-#pragma unroll
-    for (int i = 0; i < 4; ++i) W[ct.line * LS + R1 * ct.g + pass_out<R1>(i, ct)] = v[i];
-    __syncthreads();
-    get_strided(v, sr);
+    put_contiguous(in_row, v);
+    line_sync();
+    get_strided(in_row, v, sr);
     twiddle(v, wri);
     group_dft<R2, true>(v, sr);
     wave_order();
-    put_strided(v, sr);
-    __syncthreads();
+    put_strided(in_row, v, sr);
+    line_sync();
     cx<float> qb[4], zb[4], rb[4];
     int r0, c0;
     ChainRows<M>::origin(tid, 0, r0, c0);
@@ -560,9 +625,13 @@ __global__ __launch_bounds__((ChainMulti<M, V>::NT)) void k_chain_multi(StepArgs
         Rv[e] = rb[e];
       }
     };
-    const ChainSink<M, LS> sink{window_of(sl), bw, a.n, line0, sent, shared_l2, Q};
-    pixel_update_body<M, ChainRows<M>, L, false, kObject>(a, 0, tid, line0, load, qqmax, zmax, sink);
-    pixel_update_body<M, ChainRows<M>, L, false, kProbe>(a, 0, tid, line0, load, qqmax, zmax, sink);
+    const ChainSink<M, LS, SOLO> sink{window_of(sl), bw, a.n, line0, sent, shared_l2, Q, Z};
+    if constexpr (SOLO) {
+      pixel_update_body<M, ChainRows<M>, L, false>(a, 0, tid, line0, load, qqmax, zmax, sink);
+    } else {
+      pixel_update_body<M, ChainRows<M>, L, false, kObject>(a, 0, tid, line0, load, qqmax, zmax, sink);
+      pixel_update_body<M, ChainRows<M>, L, false, kProbe>(a, 0, tid, line0, load, qqmax, zmax, sink);
+    }
     __syncthreads();  // the probe rows are written, Z and W read
     before = sl;
     sl = next;

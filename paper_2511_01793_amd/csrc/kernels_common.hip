@@ -47,6 +47,22 @@ __global__ __launch_bounds__(256) void k_fill_c64(float2* p, size_t count, float
   if (i < count) p[i] = v;
 }
 
+// No sequence number of an earlier launch may be found in the scratch (a captured launch is
+// replayed with the same numbers).  One workgroup alone (m = 32) uses only the counters.
+__global__ __launch_bounds__(256) void k_chain_clear(float4* p, int count, double* sampled) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < count) p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (i == 0 && sampled) *sampled = 0.0;
+}
+
+hipError_t launch_chain_clear(int m, float2* scratch, double* sampled, hipStream_t s) {
+  const size_t all = chain_clear_units(m), first = m == 32 ? all - kChainCounterUnits : 0;
+  const int count = (int)(all - first);
+  hipLaunchKernelGGL(k_chain_clear, dim3((count + 255) / 256), dim3(256), 0, s,
+                     reinterpret_cast<float4*>(scratch) + first, count, sampled);
+  return hipGetLastError();
+}
+
 hipError_t launch_slot_info(const int* idx, const int2* pos, int n_pos, int4* slot, int count,
                             hipStream_t s) {
   hipLaunchKernelGGL(k_slot_info, dim3((count + 255) / 256), dim3(256), 0, s, idx, pos, n_pos, slot,

@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256) void k256_rows_inv(StepArgs a) {
           Rv[2 * i + 1] = A[(r0 - row0 + i) * LSR + c0 + 1];
         }
       },
-      qqmax, zmax, ToSlots{});
+      qqmax, zmax);
 }
 
 // per-pattern terms from the 16 partial sums of its column blocks (or strips), in

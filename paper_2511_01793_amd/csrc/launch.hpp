@@ -109,19 +109,21 @@ struct ChainSync {
 // each; the maxima of every wave; the workgroups' XCDs; the counters; then (not cleared) the misfit terms of the
 // last kChainTermSteps steps, m^2 floats each.  None for the probe sides without it.
 constexpr int kChainTermSteps = 4;
-constexpr size_t chain_clear_units(int m) { return 3 * (size_t)m * m + 64 + 32 + 16; }
+constexpr int kChainCounterUnits = 16;
+constexpr size_t chain_clear_units(int m) { return 3 * (size_t)m * m + 64 + 32 + kChainCounterUnits; }
 inline size_t chain_scratch_bytes(int m) {
-  if (m != 64 && m != 128) return 0;
+  if (m > 128) return 0;  // no sequential sweep
   return chain_clear_units(m) * 16 + (size_t)kChainTermSteps * m * m * 4;
 }
 
 // One launch runs a whole sequential sweep (minibatch 1): a.slot points at n_steps
 // slots; each step's update is applied directly to the object window and the probe.
-// Plans of 8- and 16-point passes at m = 64 and 128 run on several workgroups
-// (kernels_chain.hpp), which exchange data through y.scratch (cleared on the stream
-// first); the others on one.
+// At m = 64 and 128 several workgroups share a step (kernels_chain.hpp).  y.scratch and
+// a.sampled are cleared on the stream first.
 hipError_t launch_chain_sweep(int m, int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
                               hipStream_t s);
+// its clearing of the scratch and of *sampled (nullable)
+hipError_t launch_chain_clear(int m, float2* scratch, double* sampled, hipStream_t s);
 
 // misfit terms, unreduced: of all patterns (slot == nullptr; count = N, pattern k at
 // pos[k]) or of the count patterns of a slot list -> phi_out (count doubles): term j of

@@ -1,4 +1,4 @@
-"""Sequential sweeps spread over several workgroups (m = 64 and 128): bitwise the fused path with
+"""Sequential sweeps (minibatch 1, one launch; several workgroups at m = 64 and 128): bitwise the fused path with
 minibatch 1 in every option, window overlaps of every kind, two sweeps at once, and the error path."""
 import numpy as np
 import pytest
@@ -41,7 +41,8 @@ def same(a, b):
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and a[2] == b[2]
 
 
-@pytest.mark.parametrize("m, v", [(64, 0), (64, 3), (128, 0), (128, 1), (128, 2)])
+@pytest.mark.parametrize("m, v", [(32, 0), (32, 1), (64, 0), (64, 1), (64, 2), (64, 3), (128, 0),
+                                  (128, 1), (128, 2)])
 @pytest.mark.parametrize("kw", [dict(levels=1), dict(levels=3), dict(joint_step=False, levels=1),
                                 dict(update_probe=False), dict(alpha_z=0.5), dict(alpha=0.0),
                                 dict(zero_phase_memory=True)], ids=str)
@@ -51,7 +52,7 @@ def test_every_option_is_bitwise_the_fused_path(m, v, kw):
     same(sweep(p, "fused", fft_plan=v, **kw), sweep(p, "chain", fft_plan=v, **kw))
 
 
-@pytest.mark.parametrize("m", [64, 128])
+@pytest.mark.parametrize("m", [32, 64, 128])
 @pytest.mark.parametrize("kind", ["same", "disjoint", "one pixel", "row apart", "rectangular", "single"])
 def test_window_overlaps(m, kind):
     """Successive windows that coincide, do not meet, share one pixel or all but one row, on a
