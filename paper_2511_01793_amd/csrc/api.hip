@@ -127,6 +127,22 @@ struct Layout {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// Tiles in the stack buffer: a minibatch's, and at m = 256, where the full misfit and the
+// gradient run through it in chunks too, up to 256 (128 MB, half of the Infinity Cache).
+// Chunks of a minibatch left most of the chip idle between launches; full misfit of 961
+// patterns in chunks of 32: 501 us, 64: 375, 128: 314, 256: 285.  The gradient also keeps two
+// slot buffers per chunk and is fastest at 128 (411 patterns: 24: 870 us, 64: 500, 128: 440, 256: 452).
+constexpr size_t kMisfitChunk256 = 256, kGradChunk256 = 128;
+size_t stack_slots(const emagpie_config& c) {
+  const size_t B = (size_t)c.minibatch, N = (size_t)c.n_pos;
+  return c.m == 256 ? std::max(B, std::min(N, kMisfitChunk256)) : B;
+}
+// patterns per chunk when n are taken in as few chunks of at most `most` as there have to be
+size_t even_chunk(size_t n, size_t most) {
+  const size_t chunks = (n + most - 1) / most;
+  return (n + chunks - 1) / chunks;
+}
+
 Layout make_layout(const emagpie_config& c) {
   Layout L{};
   size_t cur = 0;
@@ -135,7 +151,7 @@ Layout make_layout(const emagpie_config& c) {
     cur += align256(bytes);
     return r;
   };
-  const size_t m2 = (size_t)c.m * c.m, N = (size_t)c.n_pos, B = (size_t)c.minibatch;
+  const size_t m2 = (size_t)c.m * c.m, N = (size_t)c.n_pos, B = (size_t)c.minibatch, SB = stack_slots(c);
   L.dperm = take(N * m2 * 4);
   L.pos = take(N * 8);
   L.slots = take(std::max(N, B) * 16);
@@ -147,15 +163,16 @@ Layout make_layout(const emagpie_config& c) {
   L.pden = take(B * m2 * 4);
   L.pden_slot = take(B * 4);
   L.phi = take(B * 8);
-  L.stack = take(B * m2 * 8);
+  L.stack = take(SB * m2 * 8);
   L.zmax = take(B * 4);
   L.ubuf = take(m2 * 4);
   L.Dbuf = take(m2 * 4);
   L.scal = take(256);
   L.bar = take(256);
   L.phi_all = take(N * 8);
-  // patterns per gradient chunk: at m = 256 the stack buffer's minibatch
-  L.grad_chunk = (int)std::min<size_t>(N, c.m == 256 ? B : c.m == 128 ? 256 : emg::kMaxSlots);
+  L.grad_chunk = (int)(c.m == 256   ? even_chunk(N, kGradChunk256)
+                       : c.m == 128 ? std::min<size_t>(N, 256)
+                                    : std::min<size_t>(N, emg::kMaxSlots));
   const size_t gel = c.m <= 64 ? 16 : 8;  // complex128 where the float64 gradient exists
   L.gz = take((size_t)L.grad_chunk * m2 * gel);
   L.gq = take((size_t)L.grad_chunk * m2 * gel);
@@ -164,8 +181,8 @@ Layout make_layout(const emagpie_config& c) {
   L.tune_obj = take(tune ? (size_t)c.n_rows * c.n_cols * 8 : 0);
   L.tune_probe = take(tune ? m2 * 8 : 0);
   L.phase = take(c.zero_phase_memory ? N * m2 * 8 : 0);
-  // m = 256: strip maxima and column-block partial misfits per slot (16 of each)
-  L.part = take(c.m == 256 ? B * 16 * (4 + 4 + 8) : 0);
+  // m = 256: per slot the strip maxima, per slot or pattern the column-block misfits (16 of each)
+  L.part = take(c.m == 256 ? SB * 16 * (4 + 4) + std::max(SB, N) * 16 * 8 : 0);
   // what a sequential sweep's workgroups exchange (minibatch 1)
   L.chain = take(B == 1 ? emg::chain_scratch_bytes(c.m) : 0);
   L.total = cur;
@@ -320,10 +337,10 @@ emg::StepArgs base_args(emagpie_ctx c, void* obj, void* probe) {
   a.phase_write = 1;
   if (c->cfg.m == 256) {
     uint8_t* p = c->ws + c->lay.part.off;
-    const size_t B = (size_t)c->cfg.minibatch;
+    const size_t SB = stack_slots(c->cfg);
     a.part_q = reinterpret_cast<float*>(p);
-    a.part_z = reinterpret_cast<float*>(p + B * 16 * 4);
-    a.part_phi = reinterpret_cast<double*>(p + B * 16 * 8);
+    a.part_z = reinterpret_cast<float*>(p + SB * 16 * 4);
+    a.part_phi = reinterpret_cast<double*>(p + SB * 16 * 8);
   }
   a.tw = c->tw32;
   a.numer = c->numer;
@@ -1144,12 +1161,10 @@ emagpie_status emagpie_misfit(emagpie_ctx ctx, const void* obj_dev, const void* 
   if (!obj_dev || !probe_dev || !misfit_dev) return fail(EMAGPIE_E_ARG, "null argument");
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (ctx->cfg.m == 256) {
-    // strips and column blocks over the stack buffer, minibatch-sized chunks of patterns
+    // strips and column blocks over the stack buffer, in chunks of patterns
     const emg::StepArgs a = base_args(ctx, const_cast<void*>(obj_dev), const_cast<void*>(probe_dev));
-    for (int k0 = 0; k0 < ctx->cfg.n_pos; k0 += ctx->cfg.minibatch) {
-      const int cnt = std::min(ctx->cfg.minibatch, ctx->cfg.n_pos - k0);
-      EMG_HIP(emg::launch_misfit_strips(256, a, k0, cnt, ctx->phi_all + k0, s));
-    }
+    EMG_HIP(emg::launch_misfit256(a, ctx->cfg.n_pos, (int)even_chunk(ctx->cfg.n_pos, stack_slots(ctx->cfg)),
+                                  ctx->phi_all, s));
     EMG_HIP(emg::launch_sum_doubles(ctx->phi_all, ctx->cfg.n_pos, misfit_dev, s));
     return EMAGPIE_OK;
   }

@@ -125,6 +125,13 @@ __device__ __forceinline__ double block_sum(double v, double* red, int tid) {
   return v;
 }
 
+// LDS written and read inside one wave: its LDS accesses execute in order, so only the
+// compiler has to keep them in order
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // sum over the four consecutive lanes of a 4 x 4 region (identical in all four)
 __device__ __forceinline__ float quad_sum(float v) {
   v += dpp_f<kDppQuadXor1>(v);
@@ -1680,7 +1687,8 @@ __global__ __launch_bounds__(256) void k_layout(const float* d, float* dperm, do
   double acc = 0.0;
   int nonfinite = 0;
   for (int e = tid; e < M * M; e += 256) {
-    const float v = src[freq_of_pos<M, V>(e / M) * M + freq_of_pos<M, V>(e % M)];
+    // (m = 256 keeps its columns in natural order, as its strip kernels do)
+    const float v = src[freq_of_pos<M, V>(e / M) * M + (M == 256 ? e % M : freq_of_pos<M, V>(e % M))];
     dst[e] = fmaxf(v, 0.f);  // amplitude() takes the root of this without a test
     nonfinite |= !isfinite(v);
     acc += (double)v;

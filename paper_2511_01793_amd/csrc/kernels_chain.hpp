@@ -384,10 +384,6 @@ __global__ __launch_bounds__((Chain<M, V>::NT)) void k_chain(StepArgs a, int n_s
   // the values of a pass in W: points g + R1 j (strided) or R1 g + j (contiguous) of a
   // line, a column's in a row of W of their own or (the one workgroup) down W.  An item's lanes lie in one wave, so an item goes back to where it was read
   // without a block barrier; wave_order keeps the compiler from moving the accesses.
-  auto wave_order = []() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  };
   auto line_sync = [&]() {
     if constexpr (SOLO) wave_order();
     else __syncthreads();

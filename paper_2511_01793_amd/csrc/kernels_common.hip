@@ -157,11 +157,6 @@ hipError_t launch_chain_sweep(int m, int v, int L, const StepArgs& a, int n_step
                               hipStream_t s) {
   EMG_BY_M(m, chain(v, L, a, n_steps, y, s));
 }
-hipError_t launch_misfit_strips(int m, const StepArgs& a, int k0, int count, double* phi_out,
-                                hipStream_t s) {
-  if (m != 256) return hipErrorInvalidValue;
-  return Launchers256::misfit_strips(a, k0, count, phi_out, s);
-}
 hipError_t launch_grad(int m, int v, bool f64, const GradArgs& g, hipStream_t s) {
   EMG_BY_M(m, grad(v, f64, g, s));
 }

@@ -10,16 +10,41 @@
 //   3. row strips:    inverse row passes, then the per-pixel surrogate algebra of
 //                     the strip (multigrid blocks of 2 x 2 and 4 x 4 never cross a
 //                     strip of 16 rows), numerators for the finalize.
-// The radix split is 16 x 16 in both directions, so the transform order (and the
-// amplitude layout) is that of the plan (256, 0).  The finalize, layout and
-// normalisation kernels are the shared templates.
+// Every pass is 16 points per thread, and a strip goes through LDS only where its points
+// change threads: the column blocks and the inverse row passes start from memory in registers,
+// and every last pass writes from them.  The
+// stack buffer keeps rows in natural order and columns in frequency order: transform
+// position 16 k + j of the 16 x 16 split is frequency k + 16 j, so the lanes k of one output j
+// write 16 neighbours, and a column block reads 16 neighbours of every row.  The measured
+// intensities are laid out the same way (rows in transform order, columns in natural order).
+// Measured (961 patterns of 256^2, minibatch 32): the sweep's stages 31.3 -> 29.9 us per
+// minibatch against passes that all went through LDS; the full misfit, in chunks of up to 256
+// patterns instead of a minibatch's, 555 -> 285 us.
+// The finalize, layout and normalisation kernels are the shared templates.
 #include "kernels.hpp"
 
 namespace emg {
 
 namespace big {
-constexpr int M = 256, S = 16, NT = 256, LSR = M + 1, LSC = S + 1;
+constexpr int M = 256, S = 16, NT = 256;
 constexpr int R1 = Plan<256, 0>::R1, R2 = Plan<256, 0>::R2;
+static_assert(R1 == 16 && R2 == 16, "16-point passes");
+// LDS strides and padding without bank conflicts: a strip as rows of padded positions, a
+// column block as positions of 17
+constexpr int LSR = M + 16, LSC = S + 1;
+__device__ __forceinline__ int pad(int p) { return p + p / 16; }
+
+// The strided passes of group g.  The twiddles come from the table in LDS: 15 loads per
+// thread from the global one, as many as the pass's data, cost 4-5% of a sweep.
+__device__ __forceinline__ void twiddle_forward(cx<float>* v, const cx<float>* tws, int g) {
+#pragma unroll
+  for (int j = 1; j < 16; ++j) v[j] = mul_fma(tws[g * j], v[j]);
+}
+__device__ __forceinline__ void strided_inverse(cx<float>* v, const cx<float>* tws, int g) {
+#pragma unroll
+  for (int j = 1; j < 16; ++j) v[j] = mul_fma(conjg(tws[g * j]), v[j]);
+  dft16<float, true>(v);
+}
 
 // thread's 2 x 2 blocks in a 16 x 256 strip: four rounds of 16 x 64 pixels side by
 // side; four consecutive lanes own one 4 x 4 region
@@ -33,20 +58,29 @@ struct StripLayout {
 };
 }  // namespace big
 
-// Every kernel below runs (slot, strip) pairs strip-major: block i takes slot
-// i mod b and strip i / b, so with b a multiple of the XCD count all strips of a
-// slot run on one XCD (block i runs on XCD i mod 8), beside the slots listed next
-// to it, and the overlapping windows' object rows meet in that XCD's L2.
+// Every kernel below runs (slot, strip) pairs strip-major: with nsl, the slot count a.b
+// rounded up to a multiple of the XCD count, block i takes slot i mod nsl and strip i / nsl.
+// All strips of a slot then run on one XCD (block i runs on XCD i mod 8), beside the
+// slots listed next to it, and the overlapping windows' object rows and the slot's stack
+// columns meet in that XCD's L2 (full misfit in chunks of 241 patterns: 303 us without the
+// rounding, 279 us with it).  What the first loads need comes as leading arguments, in
+// scalar registers at dispatch (see k_patch_step); a copy in the record is not used.
 //
 // 1. psi and forward row passes of strip rb of slot s (or of pattern k0 + s when
 // a.slot is null: the misfit over all patterns)
-__global__ __launch_bounds__(256) void k256_rows_fwd(StepArgs a, int k0) {
+__global__ __launch_bounds__(256) void k256_rows_fwd(int nsl, int b, const int4* slot, float2* obj, int n, float2* probe, StepArgs rec, int k0) {
+  StepArgs a = rec;
+  a.slot = slot;
+  a.obj = obj;
+  a.n = n;
+  a.probe = probe;
   using namespace big;
   __shared__ cx<float> A[S * LSR];
   __shared__ cx<float> tws[M];
   __shared__ float redf[2 * NT / 64];
-  const int tid = threadIdx.x, nsl = gridDim.x / S, s = blockIdx.x % nsl, rb = blockIdx.x / nsl,
+  const int tid = threadIdx.x, s = blockIdx.x % nsl, rb = blockIdx.x / nsl,
             row0 = rb * S;
+  if (s >= b) return;
   int wr, wc;
   if (a.slot) {
     const int4 sl = a.slot[s];
@@ -57,34 +91,47 @@ __global__ __launch_bounds__(256) void k256_rows_fwd(StepArgs a, int k0) {
     wr = p.x;
     wc = p.y;
   }
+  const int row = tid / 16, g = tid % 16, ln = tid & 63, wave = tid >> 6;
   tws[tid] = ld(a.tw, tid);
-  const float2* zwin = a.obj + (size_t)wr * a.n + wc;
+  // Four rows per wave, loaded 64 pixels at a time: the window's alignment is arbitrary,
+  // and runs of 16 pixels (the first pass's own points) would each cross a cache line.  The
+  // wave's rows stay its own, so its passes need no block barrier between them.
+  const float2* zwin = a.obj + (size_t)(wr + row0) * a.n + wc;
   float q2m = 0.f, z2m = 0.f;
 #pragma unroll
-  for (int r = 0; r < S; ++r) {
-    const cx<float> q = ld(a.probe, (size_t)(row0 + r) * M + tid);
-    const cx<float> zz = ld(zwin, (size_t)(row0 + r) * a.n + tid);
+  for (int i = 0; i < 16; ++i) {
+    const int r = 4 * wave + i / 4, c = ln + 64 * (i % 4);
+    const cx<float> q = ld(a.probe, (row0 + r) * M + c), z = ld(zwin, (size_t)r * a.n + c);
     q2m = fmaxf(q2m, norm2(q));
-    z2m = fmaxf(z2m, norm2(zz));
-    A[r * LSR + tid] = mul(q, zz);
+    z2m = fmaxf(z2m, norm2(z));
+    A[r * LSR + pad(c)] = mul(q, z);
   }
+  wave_order();
+  cx<float> v[16];
+  cx<float>* L = A + row * LSR;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) v[j] = L[pad(g + 16 * j)];
+  dft16<float, false>(v);
+  __syncthreads();  // the table is staged
+  twiddle_forward(v, tws, g);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) L[pad(g + 16 * j)] = v[j];
+  wave_order();
+  // contiguous pass of run g; its output j is frequency g + 16 j
+#pragma unroll
+  for (int j = 0; j < 16; ++j) v[j] = L[pad(16 * g + j)];
+  dft16<float, false>(v);
   wave_max2_to_lds<NT>(q2m, z2m, redf, tid);
+  const __amdgpu_buffer_rsrc_t out = through_buffer(a.stack + (size_t)s * M * M + (size_t)row0 * M, S * M);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) st_through(out, row * M + g + 16 * j, v[j]);
   __syncthreads();
-  fft_pass_lines<float, M, R1, R2, S, NT, LSR, false, true, false>(A, tws, tid);
-  __syncthreads();
-  fft_pass_lines<float, M, R1, R2, S, NT, LSR, false, false, false>(A, tws, tid);
-  __syncthreads();
-  float qm, zm;
-  lds_max2<NT>(redf, qm, zm);
   if (tid == 0) {
+    float qm, zm;
+    lds_max2<NT>(redf, qm, zm);
     a.part_q[s * S + rb] = qm;
     a.part_z[s * S + rb] = zm;
   }
-  // the strip to the stack buffer, written through the L2 (the column blocks read it
-  // in the next kernel)
-  float2* out = a.stack + (size_t)s * M * M + (size_t)row0 * M;
-#pragma unroll
-  for (int r = 0; r < S; ++r) st_through(through_buffer(out, S * M), r * M + tid, A[r * LSR + tid]);
 }
 
 // 2. column block cb of slot s: forward column passes, then in the pair pass the
@@ -93,81 +140,124 @@ __global__ __launch_bounds__(256) void k256_rows_fwd(StepArgs a, int k0) {
 // where Psi = 0, scaled by 1/m^2, with the misfit terms of the gradient's own
 // arithmetic); inverse column passes (kColsStep, kColsGrad)
 constexpr int kColsMisfit = 0, kColsStep = 1, kColsGrad = 2;
-template <int MODE>
-__global__ __launch_bounds__(256) void k256_cols(StepArgs a, int k0) {
+// PH: the step keeps a phase memory (compiled without it, two more workgroups fit a CU)
+template <int MODE, bool PH = false>
+__global__ __launch_bounds__(256) void k256_cols(int nsl, int b, const int4* slot, float2* stack, const float2* tw, const float* dperm,
+                                                 StepArgs rec, int k0) {
+  StepArgs a = rec;
+  a.slot = slot;
+  a.stack = stack;
+  a.tw = tw;
+  a.dperm = dperm;
   constexpr bool STEP = MODE == kColsStep, INVERSE = MODE != kColsMisfit;
   using namespace big;
   __shared__ cx<float> A[M * LSC];
   __shared__ cx<float> tws[M];
   __shared__ double redd[NT / 64];
-  const int tid = threadIdx.x, nsl = gridDim.x / S, s = blockIdx.x % nsl, cb = blockIdx.x / nsl,
+  const int tid = threadIdx.x, s = blockIdx.x % nsl, cb = blockIdx.x / nsl,
             col0 = cb * S;
+  if (s >= b) return;
   const int k = a.slot ? a.slot[s].x : k0 + s;
-  // the pair pass has S * R2 = NT items of R1 points: item tid, line tid % S,
-  // positions R1 (tid / S) + j; its amplitudes are loaded first
+  // item tid of every pass: column line, group (or run) g
   const int line = tid % S, g = tid / S;
-  const float* dk = a.dperm + (size_t)k * M * M;
-  float amp[R1];
-#pragma unroll
-  for (int j = 0; j < R1; ++j) amp[j] = dk[(size_t)(R1 * g + j) * M + col0 + line];
-  tws[tid] = ld(a.tw, tid);
   float2* blk = a.stack + (size_t)s * M * M + col0;
+  cx<float> v[16];
 #pragma unroll
-  for (int e = 0; e < S; ++e) {
-    const int idx = tid + e * NT, row = idx / S, cl = idx % S;
-    A[row * LSC + cl] = ld(blk, (size_t)row * M + cl);
-  }
+  for (int j = 0; j < 16; ++j) v[j] = ld(blk, (g + 16 * j) * M + line);
+  float amp[16];
+  tws[tid] = ld(a.tw, tid);
+  const float* dk = a.dperm + (size_t)k * M * M;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) amp[j] = dk[(16 * g + j) * M + col0 + line];
+  dft16<float, false>(v);
+  __syncthreads();  // the table is staged
+  twiddle_forward(v, tws, g);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) A[(g + 16 * j) * LSC + line] = v[j];
   __syncthreads();
-  fft_pass_lines<float, M, R1, R2, S, NT, LSC, false, true, true>(A, tws, tid);
-  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 16; ++j) v[j] = A[(16 * g + j) * LSC + line];
+  dft16<float, false>(v);
   double acc = 0.0;
-  float2* ph = (STEP && a.phase) ? a.phase + (size_t)k * M * M : nullptr;
-  fft_pass_lines_pair<float, M, R1, R2, S, NT, LSC, true>(A, tid, [&](int e, cx<float>& v) {
+  float2* ph = PH ? a.phase + (size_t)k * M * M : nullptr;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
     if constexpr (STEP) {
-      float2* pe = ph ? ph + (size_t)(R1 * g + e) * M + col0 + line : nullptr;
-      acc += (double)project_amp<M>(v, amplitude(amp[e]), pe, a.phase_write != 0);
+      float2* pe = PH ? ph + (16 * g + e) * M + col0 + line : nullptr;
+      acc += (double)project_amp<M>(v[e], amplitude(amp[e]), pe, a.phase_write != 0);
     } else if constexpr (MODE == kColsGrad) {
       const float am = sqrtf(fmaxf(amp[e], 0.f));
-      const float mag = sqrtf(norm2(v));
+      const float mag = sqrtf(norm2(v[e]));
       const float diff = mag - am;
       acc += (double)diff * (double)diff;
-      const cx<float> E = mag > 0.f ? scale(v, diff / mag) : cx<float>{-am, 0.f};
-      v = scale(E, 1.f / float(M * M));
+      const cx<float> E = mag > 0.f ? scale(v[e], diff / mag) : cx<float>{-am, 0.f};
+      v[e] = scale(E, 1.f / float(M * M));
     } else {
-      cx<float> t = v;
+      cx<float> t = v[e];
       acc += (double)project_amp<M>(t, amplitude(amp[e]));
     }
-  });
+  }
+  if constexpr (INVERSE) {
+    dft16<float, true>(v);
+    // back where the thread read them
+#pragma unroll
+    for (int j = 0; j < 16; ++j) A[(16 * g + j) * LSC + line] = v[j];
+  }
   acc = wave_sum(acc);
   if ((tid & 63) == 0) redd[tid >> 6] = acc;
   __syncthreads();
-  if (tid == 0) a.part_phi[s * S + cb] = lds_sum<NT>(redd);
   if constexpr (INVERSE) {
-    fft_pass_lines<float, M, R1, R2, S, NT, LSC, true, true, true>(A, tws, tid);
-    __syncthreads();
 #pragma unroll
-    for (int e = 0; e < S; ++e) {
-      const int idx = tid + e * NT, row = idx / S, cl = idx % S;
-      st_through(through_buffer(blk, M * M), row * M + cl, A[row * LSC + cl]);
-    }
+    for (int j = 0; j < 16; ++j) v[j] = A[(g + 16 * j) * LSC + line];
+    strided_inverse(v, tws, g);
+    const __amdgpu_buffer_rsrc_t out = through_buffer(blk, M * M - col0);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) st_through(out, (g + 16 * j) * M + line, v[j]);
   }
+  if (tid == 0) a.part_phi[s * S + cb] = lds_sum<NT>(redd);
+}
+
+// the inverse row passes of a strip (rows of the stack buffer at `in`): thread (row, g) ends
+// with the natural-order points g + 16 j of its row
+__device__ __forceinline__ void rows_inverse(const float2* in, const float2* tw, cx<float>* A,
+                                             cx<float>* tws, int tid, cx<float>* v) {
+  using namespace big;
+  const int row = tid / 16, g = tid % 16;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) v[j] = ld(in, row * M + g + 16 * j);
+  tws[tid] = ld(tw, tid);
+  dft16<float, true>(v);
+  cx<float>* L = A + row * LSR;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) L[pad(16 * g + j)] = v[j];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 16; ++j) v[j] = L[pad(g + 16 * j)];
+  strided_inverse(v, tws, g);
 }
 
 // 3. inverse row passes of strip rb of slot s and the strip's per-pixel algebra;
 // with STORE_R the revised exit wave R_k of the strip also goes back to the stack
 // buffer (the descent check keeps it, frozen, for the surrogate after the step)
 template <int L, bool STORE_R = false>
-__global__ __launch_bounds__(256) void k256_rows_inv(StepArgs a) {
+__global__ __launch_bounds__(256) void k256_rows_inv(int nsl, int b, const int4* slot, float2* stack, const float2* tw, float2* probe,
+                                                     StepArgs rec) {
+  StepArgs a = rec;
+  a.slot = slot;
+  a.stack = stack;
+  a.tw = tw;
+  a.probe = probe;
   using namespace big;
   __shared__ cx<float> A[S * LSR];
   __shared__ cx<float> tws[M];
-  const int tid = threadIdx.x, nsl = gridDim.x / S, s = blockIdx.x % nsl, rb = blockIdx.x / nsl,
+  const int tid = threadIdx.x, s = blockIdx.x % nsl, rb = blockIdx.x / nsl,
             row0 = rb * S;
+  if (s >= b) return;
   const int4 sl = a.slot[s];
-  tws[tid] = ld(a.tw, tid);
-  const float2* in = a.stack + (size_t)s * M * M + (size_t)row0 * M;
-#pragma unroll
-  for (int r = 0; r < S; ++r) A[r * LSR + tid] = ld(in, (size_t)r * M + tid);
+  float2* strip = a.stack + (size_t)s * M * M + (size_t)row0 * M;
+  const int row = tid / 16, g = tid % 16;
+  cx<float> v[16];
+  rows_inverse(strip, a.tw, A, tws, tid, v);
   // max |Q|^2 and max |z_k|^2 over the whole patch, from the strip maxima
   float qqmax = a.part_q[s * S], zmax = a.part_z[s * S];
 #pragma unroll
@@ -180,16 +270,13 @@ __global__ __launch_bounds__(256) void k256_rows_inv(StepArgs a) {
     for (int i = 1; i < S; ++i) t += a.part_phi[s * S + i];
     a.phi[s] = t / (2.0 * M * M);
   }
-  __syncthreads();
-  fft_pass_lines<float, M, R1, R2, S, NT, LSR, true, false, false>(A, tws, tid);
-  __syncthreads();
-  fft_pass_lines<float, M, R1, R2, S, NT, LSR, true, true, false>(A, tws, tid);
-  __syncthreads();
-  if constexpr (STORE_R) {
-    float2* outR = a.stack + (size_t)s * M * M + (size_t)row0 * M;
 #pragma unroll
-    for (int r = 0; r < S; ++r) st(outR, (size_t)r * M + tid, A[r * LSR + tid]);
+  for (int j = 0; j < 16; ++j) A[row * LSR + pad(g + 16 * j)] = v[j];
+  if constexpr (STORE_R) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) st(strip, row * M + g + 16 * j, v[j]);
   }
+  __syncthreads();
   const size_t n = (size_t)a.n;
   const float2* zwin = a.obj + (size_t)sl.y * n + sl.z;
   pixel_update_ly<M, StripLayout, L>(
@@ -200,8 +287,8 @@ __global__ __launch_bounds__(256) void k256_rows_inv(StepArgs a) {
           ld_pair(a.probe, (size_t)(r0 + i) * M + c0, q[2 * i], q[2 * i + 1]);
           zz[2 * i] = ld(zwin, (size_t)(r0 + i) * n + c0);
           zz[2 * i + 1] = ld(zwin, (size_t)(r0 + i) * n + c0 + 1);
-          Rv[2 * i] = A[(r0 - row0 + i) * LSR + c0];
-          Rv[2 * i + 1] = A[(r0 - row0 + i) * LSR + c0 + 1];
+          Rv[2 * i] = A[(r0 - row0 + i) * LSR + pad(c0)];
+          Rv[2 * i + 1] = A[(r0 - row0 + i) * LSR + pad(c0) + 1];
         }
       },
       qqmax, zmax);
@@ -221,41 +308,42 @@ __global__ __launch_bounds__(256) void k256_phi_reduce(const double* part_phi, i
 // gradient: inverse row passes of strip rb of pattern k0 + s turn the Fourier residual
 // into e_k = Q z_k - R_k; the strip's slot terms conj(Q) e_k (object) and conj(z_k) e_k
 // (probe) go to the gradient slots, for the shared reductions of k_grad_reduce
-__global__ __launch_bounds__(256) void k256_rows_grad(StepArgs a, int k0, float2* gz, float2* gq) {
+__global__ __launch_bounds__(256) void k256_rows_grad(int nsl, int b, const int2* pos, float2* stack, const float2* tw, float2* probe,
+                                                      StepArgs rec, int k0, float2* gz, float2* gq) {
+  StepArgs a = rec;
+  a.pos = pos;
+  a.stack = stack;
+  a.tw = tw;
+  a.probe = probe;
   using namespace big;
   __shared__ cx<float> A[S * LSR];
   __shared__ cx<float> tws[M];
-  const int tid = threadIdx.x, nsl = gridDim.x / S, s = blockIdx.x % nsl, rb = blockIdx.x / nsl,
+  const int tid = threadIdx.x, s = blockIdx.x % nsl, rb = blockIdx.x / nsl,
             row0 = rb * S;
+  if (s >= b) return;
   const int2 p = a.pos[k0 + s];
-  tws[tid] = ld(a.tw, tid);
-  const float2* in = a.stack + (size_t)s * M * M + (size_t)row0 * M;
+  const int row = tid / 16, g = tid % 16;
+  cx<float> v[16];
+  rows_inverse(a.stack + (size_t)s * M * M + (size_t)row0 * M, a.tw, A, tws, tid, v);
+  const float2* zrow = a.obj + (size_t)(p.x + row0 + row) * a.n + p.y + g;
+  const float2* qrow = a.probe + (row0 + row) * M + g;
+  const size_t base = (size_t)s * M * M + (size_t)(row0 + row) * M + g;
 #pragma unroll
-  for (int r = 0; r < S; ++r) A[r * LSR + tid] = ld(in, (size_t)r * M + tid);
-  __syncthreads();
-  fft_pass_lines<float, M, R1, R2, S, NT, LSR, true, false, false>(A, tws, tid);
-  __syncthreads();
-  fft_pass_lines<float, M, R1, R2, S, NT, LSR, true, true, false>(A, tws, tid);
-  __syncthreads();
-  const size_t n = (size_t)a.n, base = (size_t)s * M * M + (size_t)row0 * M;
-  const float2* zwin = a.obj + (size_t)(p.x + row0) * n + p.y;
-#pragma unroll
-  for (int r = 0; r < S; ++r) {
-    const cx<float> ev = A[r * LSR + tid];
-    const cx<float> q = ld(a.probe, (size_t)(row0 + r) * M + tid);
-    const cx<float> zz = ld(zwin, (size_t)r * n + tid);
-    st(gz, base + (size_t)r * M + tid, cmulc(q, ev));
-    st(gq, base + (size_t)r * M + tid, cmulc(zz, ev));
+  for (int j = 0; j < 16; ++j) {
+    st(gz, base + 16 * j, cmulc(ld(qrow, 16 * j), v[j]));
+    st(gq, base + 16 * j, cmulc(ld(zrow, 16 * j), v[j]));
   }
 }
 
 // descent check: 1/2 ||Q . z_k - R_k||^2 (Eq. 3 with R_k frozen in the stack buffer) of
 // strip rb of slot s at the current state; FP32 differences, FP64 sum -> part_phi
-__global__ __launch_bounds__(256) void k256_surrogate_strips(StepArgs a) {
+__global__ __launch_bounds__(256) void k256_surrogate_strips(int nsl, int b, StepArgs rec) {
+  StepArgs a = rec;
   using namespace big;
   __shared__ double redd[NT / 64];
-  const int tid = threadIdx.x, nsl = gridDim.x / S, s = blockIdx.x % nsl, rb = blockIdx.x / nsl,
+  const int tid = threadIdx.x, s = blockIdx.x % nsl, rb = blockIdx.x / nsl,
             row0 = rb * S;
+  if (s >= b) return;
   const int4 sl = a.slot[s];
   const size_t n = (size_t)a.n;
   const float2* zwin = a.obj + (size_t)(sl.y + row0) * n + sl.z;
@@ -274,34 +362,60 @@ __global__ __launch_bounds__(256) void k256_surrogate_strips(StepArgs a) {
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+static int slots_up(int b) { return (b + kDispatchXcds - 1) / kDispatchXcds * kDispatchXcds; }
+static void launch_rows_fwd(const StepArgs& a, int k0, hipStream_t s) {
+  const int nsl = slots_up(a.b);
+  hipLaunchKernelGGL(k256_rows_fwd, dim3(nsl * big::S), dim3(big::NT), 0, s, nsl, a.b, a.slot, a.obj, a.n,
+                     a.probe, a, k0);
+}
+template <int MODE, bool PH = false>
+static void launch_cols(const StepArgs& a, int k0, hipStream_t s) {
+  const int nsl = slots_up(a.b);
+  hipLaunchKernelGGL((k256_cols<MODE, PH>), dim3(nsl * big::S), dim3(big::NT), 0, s, nsl, a.b, a.slot,
+                     a.stack, a.tw, a.dperm, a, k0);
+}
+template <int L, bool STORE_R>
+static void launch_rows_inv(const StepArgs& a, hipStream_t s) {
+  const int nsl = slots_up(a.b);
+  hipLaunchKernelGGL((k256_rows_inv<L, STORE_R>), dim3(nsl * big::S), dim3(big::NT), 0, s, nsl, a.b, a.slot,
+                     a.stack, a.tw, a.probe, a);
+}
+// the three stages of a step
+template <bool STORE_R>
+static void launch_step(const StepArgs& a, int L, hipStream_t s) {
+  launch_rows_fwd(a, 0, s);
+  if (a.phase) launch_cols<kColsStep, true>(a, 0, s);
+  else launch_cols<kColsStep>(a, 0, s);
+  switch (L) {
+    case 1: launch_rows_inv<1, STORE_R>(a, s); break;
+    case 2: launch_rows_inv<2, STORE_R>(a, s); break;
+    default: launch_rows_inv<3, STORE_R>(a, s); break;
+  }
+}
+
 hipError_t Launchers256::patch_step(int v, int L, const StepArgs& a, hipStream_t s, hipEvent_t e0,
                                     hipEvent_t e1) {
   if (v != 0 || L < 1 || L > 3 || !a.part_q || !a.slot) return hipErrorInvalidValue;
-  const dim3 grid(a.b * big::S), block(big::NT);
   hipError_t e;
   if (e0 && (e = hipEventRecord(e0, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k256_rows_fwd, grid, block, 0, s, a, 0);
-  hipLaunchKernelGGL(k256_cols<kColsStep>, grid, block, 0, s, a, 0);
-  switch (L) {
-    case 1: hipLaunchKernelGGL(k256_rows_inv<1>, grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k256_rows_inv<2>, grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL(k256_rows_inv<3>, grid, block, 0, s, a); break;
-  }
+  launch_step<false>(a, L, s);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (e1 && (e = hipEventRecord(e1, s)) != hipSuccess) return e;
   return hipSuccess;
 }
 
-hipError_t Launchers256::misfit_strips(const StepArgs& a, int k0, int count, double* phi_out,
-                                       hipStream_t s) {
-  if (!a.part_q || count < 1) return hipErrorInvalidValue;
+hipError_t launch_misfit256(const StepArgs& a, int n_pos, int chunk, double* phi_out, hipStream_t s) {
+  if (!a.part_q || n_pos < 1 || chunk < 1) return hipErrorInvalidValue;
   StepArgs x = a;
   x.slot = nullptr;
-  const dim3 grid(count * big::S), block(big::NT);
-  hipLaunchKernelGGL(k256_rows_fwd, grid, block, 0, s, x, k0);
-  hipLaunchKernelGGL(k256_cols<kColsMisfit>, grid, block, 0, s, x, k0);
-  hipLaunchKernelGGL(k256_phi_reduce, dim3((count + 255) / 256), dim3(256), 0, s,
-                     (const double*)x.part_phi, count, phi_out, 1.0 / (2.0 * big::M * big::M));
+  for (int k0 = 0; k0 < n_pos; k0 += chunk) {
+    x.b = min(chunk, n_pos - k0);
+    x.part_phi = a.part_phi + (size_t)k0 * big::S;
+    launch_rows_fwd(x, k0, s);
+    launch_cols<kColsMisfit>(x, k0, s);
+  }
+  hipLaunchKernelGGL(k256_phi_reduce, dim3((n_pos + 255) / 256), dim3(256), 0, s,
+                     (const double*)a.part_phi, n_pos, phi_out, 1.0 / (2.0 * big::M * big::M));
   return hipGetLastError();
 }
 
@@ -313,47 +427,44 @@ hipError_t launch_grad256(const StepArgs& a, const GradArgs& g, hipStream_t s) {
   const int tiles = grad_tiles(g), blocks = tiles + grad_probe_blocks(M);
   for (int k0 = 0; k0 < g.n_pos; k0 += g.chunk) {
     const int cnt = min(g.chunk, g.n_pos - k0);
-    const dim3 grid(cnt * big::S), block(big::NT);
-    hipLaunchKernelGGL(k256_rows_fwd, grid, block, 0, s, x, k0);
-    hipLaunchKernelGGL(k256_cols<kColsGrad>, grid, block, 0, s, x, k0);
-    hipLaunchKernelGGL(k256_rows_grad, grid, block, 0, s, x, k0, static_cast<float2*>(g.gz_slots),
+    x.b = cnt;
+    const int nsl = slots_up(cnt);
+    x.part_phi = a.part_phi + (size_t)k0 * big::S;
+    launch_rows_fwd(x, k0, s);
+    launch_cols<kColsGrad>(x, k0, s);
+    hipLaunchKernelGGL(k256_rows_grad, dim3(nsl * big::S), dim3(big::NT), 0, s, nsl, cnt, x.pos, x.stack,
+                       x.tw, x.probe, x, k0, static_cast<float2*>(g.gz_slots),
                        static_cast<float2*>(g.gq_slots));
-    hipLaunchKernelGGL(k256_phi_reduce, dim3((cnt + 255) / 256), dim3(256), 0, s,
-                       (const double*)x.part_phi, cnt, g.phi_all + k0, 1.0 / (2.0 * M * M));
     const int first = k0 == 0;
     hipLaunchKernelGGL((k_grad_reduce<float, M>), dim3(blocks), dim3(256 * kGradZGroups), 0, s, g,
                        k0, cnt, first, tiles);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  hipLaunchKernelGGL(k256_phi_reduce, dim3((g.n_pos + 255) / 256), dim3(256), 0, s,
+                     (const double*)a.part_phi, g.n_pos, g.phi_all, 1.0 / (2.0 * M * M));
+  return hipGetLastError();
 }
 
 hipError_t launch_check256(const StepArgs& a, int levels, int finalize_shape, double* out3,
                            hipStream_t s) {
   if (!a.part_q || !a.slot || levels < 1 || levels > 3) return hipErrorInvalidValue;
-  const dim3 grid(a.b * big::S), block(big::NT);
   // the step, keeping the revised waves R_k of the state before it in the stack buffer
-  hipLaunchKernelGGL(k256_rows_fwd, grid, block, 0, s, a, 0);
-  hipLaunchKernelGGL(k256_cols<kColsStep>, grid, block, 0, s, a, 0);
-  switch (levels) {
-    case 1: hipLaunchKernelGGL((k256_rows_inv<1, true>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k256_rows_inv<2, true>), grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL((k256_rows_inv<3, true>), grid, block, 0, s, a); break;
-  }
+  launch_step<true>(a, levels, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   StepArgs f = a;
   f.sampled = out3;  // [0] += sum_k Phi_k at the state before the step
   if ((e = Launchers256::finalize(finalize_shape, f, s, nullptr, nullptr)) != hipSuccess) return e;
   // [1] surrogate of Eq. 3 at the new state against the frozen R_k
-  hipLaunchKernelGGL(k256_surrogate_strips, grid, block, 0, s, a);
+  const int nsl = slots_up(a.b);
+  hipLaunchKernelGGL(k256_surrogate_strips, dim3(nsl * big::S), dim3(big::NT), 0, s, nsl, a.b, a);
   hipLaunchKernelGGL(k256_phi_reduce, dim3((a.b + 255) / 256), dim3(256), 0, s,
                      (const double*)a.part_phi, a.b, a.phi, 0.5);
   if ((e = launch_sum_doubles(a.phi, a.b, out3 + 1, s)) != hipSuccess) return e;
   // [2] Phi_B at the new state: the batch's misfit terms through the strip kernels
-  hipLaunchKernelGGL(k256_rows_fwd, grid, block, 0, s, a, 0);
-  hipLaunchKernelGGL(k256_cols<kColsMisfit>, grid, block, 0, s, a, 0);
+  launch_rows_fwd(a, 0, s);
+  launch_cols<kColsMisfit>(a, 0, s);
   hipLaunchKernelGGL(k256_phi_reduce, dim3((a.b + 255) / 256), dim3(256), 0, s,
                      (const double*)a.part_phi, a.b, a.phi, 1.0 / (2.0 * big::M * big::M));
   if ((e = hipGetLastError()) != hipSuccess) return e;

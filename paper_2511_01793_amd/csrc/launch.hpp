@@ -159,9 +159,10 @@ struct GradArgs {
 };
 hipError_t launch_grad(int m, int v, bool f64, const GradArgs& g, hipStream_t s);
 
-// m = 256 misfit terms of patterns k0 .. k0 + count - 1 (count <= the context's
-// minibatch; uses a.stack and the part_* buffers) -> phi_out[0 .. count)
-// m = 256 gradient: chunks of g.chunk patterns (<= the context's minibatch) through the
+// m = 256 misfit terms of all patterns -> phi_out (n_pos), in chunks of at most `chunk`
+// patterns (the stack buffer's and the maxima's size; a.part_phi holds n_pos x 16)
+hipError_t launch_misfit256(const StepArgs& a, int n_pos, int chunk, double* phi_out, hipStream_t s);
+// m = 256 gradient: chunks of g.chunk patterns (at most the stack buffer's) through the
 // strip and column-block kernels over a.stack and a.part_*, then the shared reductions
 hipError_t launch_grad256(const StepArgs& a, const GradArgs& g, hipStream_t s);
 // m = 256 descent check of the minibatch a.slot / a.b: the step (revised waves kept in
@@ -169,9 +170,6 @@ hipError_t launch_grad256(const StepArgs& a, const GradArgs& g, hipStream_t s);
 // by the caller, out3[0] accumulated by the finalize
 hipError_t launch_check256(const StepArgs& a, int levels, int finalize_shape, double* out3,
                            hipStream_t s);
-
-hipError_t launch_misfit_strips(int m, const StepArgs& a, int k0, int count, double* phi_out,
-                                hipStream_t s);
 
 // Calibration kernels (kernels_peak.hip): a copy of n4 16-byte elements with `blocks`
 // workgroups of 256 threads, and a loop of independent FP32 FMAs (iters rounds of 16 per
@@ -240,8 +238,6 @@ struct Launchers256 {
   static hipError_t grad(int v, bool f64, const GradArgs& g, hipStream_t s);
   static hipError_t chain(int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
                           hipStream_t s);
-  static hipError_t misfit_strips(const StepArgs& a, int k0, int count, double* phi_out,
-                                  hipStream_t s);
 };
 
 }  // namespace emg
