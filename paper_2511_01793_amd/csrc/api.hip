@@ -121,7 +121,7 @@ bool wants_tuning(const emagpie_config& c) {
 struct Layout {
   Region dperm, pos, slots, morder, tw32, tw64, numer, pnum, pden, pden_slot, phi, stack, zmax, ubuf, Dbuf,
       scal, bar, phi_all, gz, gq, tune_obj, tune_probe, phase, part, chain;
-  int grad_chunk;
+  int grad_chunk, grad_probe_slots;
   size_t total;
 };
 
@@ -170,12 +170,11 @@ Layout make_layout(const emagpie_config& c) {
   L.scal = take(256);
   L.bar = take(256);
   L.phi_all = take(N * 8);
-  L.grad_chunk = (int)(c.m == 256   ? even_chunk(N, kGradChunk256)
-                       : c.m == 128 ? std::min<size_t>(N, 256)
-                                    : std::min<size_t>(N, emg::kMaxSlots));
+  L.grad_chunk = (int)(c.m == 256 ? even_chunk(N, kGradChunk256) : std::min<size_t>(N, emg::kMaxSlots));
+  L.grad_probe_slots = c.m == 256 ? L.grad_chunk : std::min(L.grad_chunk, emg::grad_groups(c.m));
   const size_t gel = c.m <= 64 ? 16 : 8;  // complex128 where the float64 gradient exists
   L.gz = take((size_t)L.grad_chunk * m2 * gel);
-  L.gq = take((size_t)L.grad_chunk * m2 * gel);
+  L.gq = take((size_t)L.grad_probe_slots * m2 * gel);
   // scratch state for autotuning at init (only when asked for)
   const bool tune = wants_tuning(c);
   L.tune_obj = take(tune ? (size_t)c.n_rows * c.n_cols * 8 : 0);
@@ -1197,6 +1196,7 @@ emagpie_status emagpie_grad(emagpie_ctx ctx, const void* obj_dev, const void* pr
   g.pos = ctx->pos;
   g.n_pos = ctx->cfg.n_pos;
   g.chunk = ctx->lay.grad_chunk;
+  g.probe_slots = ctx->lay.grad_probe_slots;
   g.tw = f64 ? static_cast<const void*>(ctx->tw64) : static_cast<const void*>(ctx->tw32);
   g.gobj = grad_obj_dev;
   g.gprobe = grad_probe_dev;

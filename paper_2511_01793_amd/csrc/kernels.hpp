@@ -1484,68 +1484,194 @@ __device__ __forceinline__ void stT(void* p, size_t i, cx<T> v) {
   reinterpret_cast<cx<T>*>(p)[i] = v;
 }
 
+// Patch stage of the gradient.  A workgroup takes patterns blockIdx.x, + gridDim.x, ... of
+// the chunk: each pattern's object terms conj(Q) e_k go to its own slot (the windows move), the
+// probe terms conj(z_k) e_k are added up over the workgroup's patterns in one slot, which
+// stays in its XCD's L2, so that the reduction reads one slot per workgroup.  The
+// first pass takes its points straight from memory and the last one stores from registers, a
+// run of R1 pixels per row.  512 threads at m = 64: two or more workgroups fit a CU, so the
+// loads and barriers of one overlap another's arithmetic.  What the first loads need comes as
+// preloaded arguments.  Against one pattern per workgroup with two slots each and passes all
+// through LDS: 400 patterns of 64^2 28.7 -> 25.0 us in float32, 51.0 -> 41.4 us in float64;
+// 2310 of 128^2 643 -> 481 us; 4000 of 128^2 1050 -> 747 us.
+template <typename T, int M>
+struct GradPlan {
+  static constexpr int NT = M == 128 ? 1024 : M == 64 ? 512 : 256;
+};
+
 template <typename T, int M, int V>
-__global__ __launch_bounds__((Plan<M, V>::NT)) void k_grad_patch(GradArgs g, int k0) {
-  __shared__ cx<T> A[M * lds_stride<M>()];
+__global__ __launch_bounds__((GradPlan<T, M>::NT)) void k_grad_patch(const int2* pos, const cx<T>* obj,
+                                                                    int n, const cx<T>* probe,
+                                                                    const float* dperm, const cx<T>* tw,
+                                                                    int cnt, cx<T>* gz, cx<T>* gq,
+                                                                    double* phi) {
+  constexpr int R1 = Plan<M, V>::R1, R2 = Plan<M, V>::R2, NT = GradPlan<T, M>::NT, LS = lds_stride<M>();
+  constexpr int IS = M * R1, IC = M * R2;  // items of a strided and of a contiguous pass
+  constexpr int ITS = (IS + NT - 1) / NT, ITC = (IC + NT - 1) / NT;
+  static_assert(M * M == ITS * NT * R2 || IS < NT, "whole rounds of strided items");
+  __shared__ cx<T> A[M * LS];
   __shared__ cx<T> tws[M];
-  __shared__ double redd[16];
-  constexpr int PX = Px<M, V>::PX, NT = Px<M, V>::NT, LS = Px<M, V>::LS;
-  const int tid = threadIdx.x, s = blockIdx.x, k = k0 + s;
-  const int2 pk = g.pos[k];
-  const size_t n = (size_t)g.n;
-  for (int j = tid; j < M; j += NT) tws[j] = ldT<T>(g.tw, j);
+  __shared__ double redd[NT / 64];
+  const int tid = threadIdx.x;
+  for (int j = tid; j < M; j += NT) tws[j] = tw[j];
+  // a thread's items one after another: the loads of the next one, hoisted, would spill (m = 128,
+  // 1024 threads: 528 against 482 us for the gradient of 2310 patterns)
+  auto one_at_a_time = []() {
+    if constexpr (ITS > 1) __builtin_amdgcn_sched_barrier(0);
+  };
+  // strided pass over the lines of the tile in LDS by item (line, g)
+  auto strided = [&](auto inverse, auto cols) {
+    constexpr bool INV = decltype(inverse)::value, COLS = decltype(cols)::value;
 #pragma unroll
-  for (int e = 0; e < PX; ++e) {
-    int r, c;
-    pix_rc<M, V>(tid, e, r, c);
-    A[r * LS + c] = mul(ldT<T>(g.probe, (size_t)r * M + c), ldT<T>(g.obj, (pk.x + r) * n + pk.y + c));
+    for (int it = 0; it < ITS; ++it) {
+      const int w = tid + it * NT;
+      if (IS % NT != 0 && w >= IS) break;
+      const int line = w % M, gr = w / M;
+      cx<T> v[R2];
+#pragma unroll
+      for (int j = 0; j < R2; ++j) v[j] = A[COLS ? (gr + R1 * j) * LS + line : line * LS + gr + R1 * j];
+      if constexpr (INV) {
+#pragma unroll
+        for (int j = 1; j < R2; ++j) v[j] = mul_fma(conjg(tws[gr * j]), v[j]);
+      }
+      dft_small<T, INV, R2, M>(v, tws);
+      if constexpr (!INV) {
+#pragma unroll
+        for (int j = 1; j < R2; ++j) v[j] = mul_fma(tws[gr * j], v[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < R2; ++j) A[COLS ? (gr + R1 * j) * LS + line : line * LS + gr + R1 * j] = v[j];
+      one_at_a_time();
+    }
+  };
+  auto contiguous_rows = [&](auto inverse) {
+#pragma unroll
+    for (int it = 0; it < ITC; ++it) {
+      const int w = tid + it * NT;
+      if (IC % NT != 0 && w >= IC) break;
+      cx<T>* L = A + (w % M) * LS + R1 * (w / M);
+      cx<T> v[R1];
+#pragma unroll
+      for (int j = 0; j < R1; ++j) v[j] = L[j];
+      dft_small<T, decltype(inverse)::value, R1, M>(v, tws);
+#pragma unroll
+      for (int j = 0; j < R1; ++j) L[j] = v[j];
+    }
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  for (int s = blockIdx.x; s < cnt; s += gridDim.x) {
+    const int2 pk = pos[s];
+    const cx<T>* zwin = obj + (size_t)pk.x * n + pk.y;
+    // exit wave and strided row pass; item (row i / R1, group i % R1)
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const int i = tid + it * NT, row = i / R1, gr = i % R1;
+      const bool live = IS % NT == 0 || i < IS;
+      cx<T> v[R2];
+      if (live) {
+#pragma unroll
+        for (int j = 0; j < R2; ++j)
+          v[j] = mul(probe[row * M + gr + R1 * j], zwin[(size_t)row * n + gr + R1 * j]);
+        dft_small<T, false, R2, M>(v, tws);
+      }
+      if (it == 0 && s == (int)blockIdx.x) __syncthreads();  // the twiddles are staged
+      if (!live) break;
+#pragma unroll
+      for (int j = 1; j < R2; ++j) v[j] = mul_fma(tws[gr * j], v[j]);
+      // (an earlier pattern's last pass read these places in this thread)
+#pragma unroll
+      for (int j = 0; j < R2; ++j) A[row * LS + gr + R1 * j] = v[j];
+      one_at_a_time();
+    }
+    __syncthreads();
+    contiguous_rows(no);
+    // the intensities in the order the pair pass visits them, loaded a pass ahead (two
+    // passes ahead where the registers allow it)
+    const float* dk = dperm + (size_t)s * M * M;
+    float dv[ITC][R1];
+    auto load_intensities = [&]() {
+#pragma unroll
+      for (int it = 0; it < ITC; ++it) {
+        const int w = tid + it * NT;
+        if (IC % NT != 0 && w >= IC) break;
+#pragma unroll
+        for (int j = 0; j < R1; ++j) dv[it][j] = dk[(R1 * (w / M) + j) * M + w % M];
+      }
+    };
+    if constexpr (M < 128) load_intensities();
+    __syncthreads();
+    strided(no, yes);
+    if constexpr (M == 128) load_intensities();
+    __syncthreads();
+    // last forward pass, residual in Fourier space, first inverse pass, in registers:
+    // Psi - Psi' = (|Psi| - a) Psi/|Psi|, or -a where Psi = 0
+    const T inv_m2 = T(1) / T(M * M);
+    double acc = 0.0;
+#pragma unroll
+    for (int it = 0; it < ITC; ++it) {
+      const int w = tid + it * NT;
+      if (IC % NT != 0 && w >= IC) break;
+      cx<T>* L = A + R1 * (w / M) * LS + w % M;
+      cx<T> v[R1];
+#pragma unroll
+      for (int j = 0; j < R1; ++j) v[j] = L[j * LS];
+      dft_small<T, false, R1, M>(v, tws);
+#pragma unroll
+      for (int j = 0; j < R1; ++j) {
+        const T amp = sqrt(fmax(T(dv[it][j]), T(0)));
+        const T mag = sqrt(norm2(v[j]));
+        const T diff = mag - amp;
+        acc += (double)diff * (double)diff;
+        const cx<T> E = mag > T(0) ? scale(v[j], diff / mag) : cx<T>{-amp, T(0)};
+        v[j] = scale(E, inv_m2);
+      }
+      dft_small<T, true, R1, M>(v, tws);
+#pragma unroll
+      for (int j = 0; j < R1; ++j) L[j * LS] = v[j];
+    }
+    acc = wave_sum(acc);
+    if ((tid & 63) == 0) redd[tid >> 6] = acc;
+    __syncthreads();
+    if (tid == 0) phi[s] = lds_sum<NT>(redd) / (2.0 * M * M);
+    strided(yes, yes);
+    __syncthreads();
+    contiguous_rows(yes);
+    __syncthreads();
+    // strided row pass to e_k at natural order, then the two gradient terms
+    cx<T>*gzs = gz + (size_t)s * M * M, *gqs = gq + (size_t)blockIdx.x * M * M;
+    const bool first = s == (int)blockIdx.x;
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const int i = tid + it * NT, row = i / R1, gr = i % R1;
+      if (IS % NT != 0 && i >= IS) break;
+      cx<T> v[R2], q[R2], zz[R2];
+#pragma unroll
+      for (int j = 0; j < R2; ++j) {
+        q[j] = probe[row * M + gr + R1 * j];
+        zz[j] = zwin[(size_t)row * n + gr + R1 * j];
+      }
+#pragma unroll
+      for (int j = 0; j < R2; ++j) v[j] = A[row * LS + gr + R1 * j];
+#pragma unroll
+      for (int j = 1; j < R2; ++j) v[j] = mul_fma(conjg(tws[gr * j]), v[j]);
+      dft_small<T, true, R2, M>(v, tws);
+#pragma unroll
+      for (int j = 0; j < R2; ++j) {
+        gzs[row * M + gr + R1 * j] = cmulc(q[j], v[j]);
+        v[j] = cmulc(zz[j], v[j]);
+      }
+      if (!first) {
+#pragma unroll
+        for (int j = 0; j < R2; ++j) zz[j] = gqs[row * M + gr + R1 * j];
+#pragma unroll
+        for (int j = 0; j < R2; ++j) v[j] = add(zz[j], v[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < R2; ++j) gqs[row * M + gr + R1 * j] = v[j];
+      one_at_a_time();
+    }
   }
-  // the intensities in the order the middle pass visits them (see patch_step)
-  using CP = ColPass<M, V>;
-  const float* dk = g.dperm + (size_t)k * M * M;
-  float dv[CP::PTS];
-#pragma unroll
-  for (int it = 0; it < CP::IT; ++it) {
-    const int w = tid + it * CP::NT;
-    if (CP::ITEMS < CP::NT && w >= CP::ITEMS) break;
-    const int line = w % M, gg = w / M;
-#pragma unroll
-    for (int j = 0; j < CP::R1; ++j) dv[it * CP::R1 + j] = dk[(CP::R1 * gg + j) * M + line];
-  }
-  __syncthreads();
-  fft_pass<T, M, V, false, true, false>(A, tws, tid);
-  __syncthreads();
-  fft_pass<T, M, V, false, false, false>(A, tws, tid);
-  __syncthreads();
-  fft_pass<T, M, V, false, true, true>(A, tws, tid);
-  __syncthreads();
-  // last forward pass, residual in Fourier space, first inverse pass, in registers:
-  // Psi - Psi' = (|Psi| - a) Psi/|Psi|, or -a where Psi = 0
-  const T inv_m2 = T(1) / T(M * M);
-  double acc = 0.0;
-  fft_pass_pair<T, M, V>(A, tid, [&](int e, cx<T>& P) {
-    const T amp = sqrt(fmax(T(dv[e]), T(0)));
-    const T mag = sqrt(norm2(P));
-    const T diff = mag - amp;
-    acc += (double)diff * (double)diff;
-    const cx<T> E = mag > T(0) ? scale(P, diff / mag) : cx<T>{-amp, T(0)};
-    P = scale(E, inv_m2);
-  });
-  __syncthreads();
-  fft2_inverse_tail<T, M, V>(A, tws, tid);
-  const size_t base = (size_t)s * M * M;
-#pragma unroll
-  for (int e = 0; e < PX; ++e) {
-    int r, c;
-    pix_rc<M, V>(tid, e, r, c);
-    const cx<T> ev = A[r * LS + c];
-    const cx<T> q = ldT<T>(g.probe, (size_t)r * M + c);
-    const cx<T> zz = ldT<T>(g.obj, (pk.x + r) * n + pk.y + c);
-    stT<T>(g.gz_slots, base + r * M + c, cmulc(q, ev));
-    stT<T>(g.gq_slots, base + r * M + c, cmulc(zz, ev));
-  }
-  const double tot = block_sum<NT>(acc, redd, tid);
-  if (tid == 0) g.phi_all[k] = tot / (2.0 * M * M);
 }
 
 // Deterministic reductions of the per-pattern gradient slots.  Both split a
@@ -1623,7 +1749,7 @@ __device__ __forceinline__ void grad_scatter_tile(const GradArgs& g, int k0, int
 // this once, for the barrier)
 template <typename T, int M>
 __device__ __forceinline__ void grad_probe_unit(const GradArgs& g, int cnt, int first, int unit,
-                                                cx<T>* part, int tid) {
+                                                cx<T>* part, int tid) {  // cnt slots of probe sums
   constexpr int G = kGradQGroups, PPU = 256 / G, U = 8;
   const int gi = tid / PPU, lp = tid % PPU;
   const int r = unit * PPU + lp;
@@ -1663,13 +1789,14 @@ inline int grad_probe_blocks(int m) {
 }
 template <typename T, int M>
 __global__ __launch_bounds__(256 * kGradZGroups) void k_grad_reduce(GradArgs g, int k0, int cnt,
-                                                                     int first, int tiles) {
+                                                                     int probe_slots, int first,
+                                                                     int tiles) {
   __shared__ cx<T> part[256 * kGradZGroups];
   const int tid = threadIdx.x;
   if ((int)blockIdx.x < tiles)
     grad_scatter_tile<T, M>(g, k0, cnt, first, blockIdx.x, part, tid);
   else
-    grad_probe_unit<T, M>(g, cnt, first,
+    grad_probe_unit<T, M>(g, probe_slots, first,
                           ((int)blockIdx.x - tiles) * kGradUnitsPerBlock + (tid >> 8),
                           part + (tid & ~255), tid & 255);
 }
@@ -2007,14 +2134,16 @@ hipError_t Launchers<M>::chain(int v, int L, const StepArgs& a, int n_steps, con
 
 template <typename T, int M, int V>
 static hipError_t grad_t(const GradArgs& g, hipStream_t s) {
-  constexpr int NT = Plan<M, V>::NT;
   const int tiles = grad_tiles(g), blocks = tiles + grad_probe_blocks(M);
   for (int k0 = 0; k0 < g.n_pos; k0 += g.chunk) {
-    const int cnt = min(g.chunk, g.n_pos - k0);
+    const int cnt = min(g.chunk, g.n_pos - k0), groups = min(cnt, g.probe_slots);
     const int first = k0 == 0;
-    hipLaunchKernelGGL((k_grad_patch<T, M, V>), dim3(cnt), dim3(NT), 0, s, g, k0);
+    hipLaunchKernelGGL((k_grad_patch<T, M, V>), dim3(groups), dim3(GradPlan<T, M>::NT), 0, s, g.pos + k0,
+                       static_cast<const cx<T>*>(g.obj), g.n, static_cast<const cx<T>*>(g.probe),
+                       g.dperm + (size_t)k0 * M * M, static_cast<const cx<T>*>(g.tw), cnt,
+                       static_cast<cx<T>*>(g.gz_slots), static_cast<cx<T>*>(g.gq_slots), g.phi_all + k0);
     hipLaunchKernelGGL((k_grad_reduce<T, M>), dim3(blocks), dim3(256 * kGradZGroups), 0, s, g, k0,
-                       cnt, first, tiles);
+                       cnt, groups, first, tiles);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -437,7 +437,7 @@ hipError_t launch_grad256(const StepArgs& a, const GradArgs& g, hipStream_t s) {
                        static_cast<float2*>(g.gq_slots));
     const int first = k0 == 0;
     hipLaunchKernelGGL((k_grad_reduce<float, M>), dim3(blocks), dim3(256 * kGradZGroups), 0, s, g,
-                       k0, cnt, first, tiles);
+                       k0, cnt, cnt, first, tiles);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -153,11 +153,14 @@ struct GradArgs {
   const void* tw;      // twiddles in the gradient precision
   void* gobj;          // nr x n
   void* gprobe;        // m x m
+  int probe_slots;     // slots of gq: workgroups of the patch stage (m = 256: patterns)
   void* gz_slots;      // chunk x m^2
-  void* gq_slots;      // chunk x m^2
+  void* gq_slots;      // probe_slots x m^2
   double* phi_all;     // N
 };
 hipError_t launch_grad(int m, int v, bool f64, const GradArgs& g, hipStream_t s);
+// patch-stage workgroups of the gradient at probe side m < 256 (k_grad_patch)
+constexpr int grad_groups(int m) { return m == 128 ? 256 : m == 64 ? 512 : 1024; }
 
 // m = 256 misfit terms of all patterns -> phi_out (n_pos), in chunks of at most `chunk`
 // patterns (the stack buffer's and the maxima's size; a.part_phi holds n_pos x 16)
