@@ -1203,13 +1203,13 @@ emagpie_status emagpie_grad(emagpie_ctx ctx, const void* obj_dev, const void* pr
   g.gz_slots = ctx->ws + ctx->lay.gz.off;
   g.gq_slots = ctx->ws + ctx->lay.gq.off;
   g.phi_all = ctx->phi_all;
+  g.misfit = misfit_dev;
   if (ctx->cfg.m == 256) {
     const emg::StepArgs a = base_args(ctx, const_cast<void*>(obj_dev), const_cast<void*>(probe_dev));
     EMG_HIP(emg::launch_grad256(a, g, s));
   } else {
     EMG_HIP(emg::launch_grad(ctx->cfg.m, ctx->cfg.fft_plan, f64, g, s));
   }
-  if (misfit_dev) EMG_HIP(emg::launch_sum_doubles(ctx->phi_all, ctx->cfg.n_pos, misfit_dev, s));
   return EMAGPIE_OK;
 }
 

@@ -1674,11 +1674,37 @@ __global__ __launch_bounds__((GradPlan<T, M>::NT)) void k_grad_patch(const int2*
   }
 }
 
+// sum of `count` doubles by 256 threads (redd: 16 doubles): thread t adds in[t],
+// in[t + 256], ... in that order; eight loads in flight per round
+__device__ __forceinline__ void sum_doubles(const double* in, int count, double* out, double* redd,
+                                            int tid) {
+  constexpr int U = 8;
+  double acc = 0.0;
+  for (int i0 = tid; i0 < count; i0 += 256 * U) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i0 + 256 * u < count ? in[i0 + 256 * u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + 256 * u < count) acc += v[u];
+  }
+  const double tot = block_sum<256>(acc, redd, tid);
+  if (tid == 0) out[0] = tot;
+}
+
 // Deterministic reductions of the per-pattern gradient slots.  Both split a
 // chunk's patterns into contiguous groups summed in parallel (ascending order
 // inside a group) and add the group partials in group order, with several loads
 // in flight per round; the order depends only on the chunk, not on the launch.
-constexpr int kGradTile = 16;   // object gradient tiles kGradTile^2
+// Object gradient tiles of 256 pixels.  Rows of 256 bytes (32 columns) cross into fewer lines
+// that the next tile reads as well, square ones are reached by fewer patterns: 2310 patterns of
+// 128^2 463 us with 8 x 32 tiles, 477 us with 16 x 16; 300 of 32^2 18.2 and 16.2 us, 400 of 64^2
+// 23.8 and 23.4 us.  (Runs of tiles on one XCD, for those lines: its share of crowded tiles made
+// the call 10-25% slower.)
+template <int M>
+struct GradTile {
+  static constexpr int Y = M >= 128 ? 8 : 16, X = 256 / Y;
+};
 constexpr int kGradZGroups = 4; // pattern groups per object tile (one per 256 threads)
 constexpr int kGradQGroups = 16;  // pattern groups per probe pixel
 
@@ -1686,24 +1712,24 @@ __device__ __forceinline__ void settle2(int2& v) {
   asm volatile("" : "+v"(v.x), "+v"(v.y));
 }
 
-// object gradient: tile `tile` of kGradTile^2 pixels, kGradZGroups x 256 threads
+// object gradient: tile `tile` of 256 pixels, kGradZGroups x 256 threads
 template <typename T, int M>
-__device__ __forceinline__ void grad_scatter_tile(const GradArgs& g, int k0, int cnt, int first,
-                                                  int tile, cx<T>* part, int tid) {
-  constexpr int TS = kGradTile, GS = kGradZGroups, U = 8;
-  static_assert(TS * TS == 256, "one pixel per thread of a group");
-  const int gi = tid >> 8, q = tid & 255, lane = tid & 63, n = g.n, nr = g.nr;
-  const int tpr = (n + TS - 1) / TS;
-  const int ty = (tile / tpr) * TS, tx = (tile % tpr) * TS;
-  const int y = ty + q / TS, x = tx + q % TS;
+__device__ __forceinline__ void grad_scatter_tile(const int2* pos, const cx<T>* gz, cx<T>* gobj, int n,
+                                                  int nr, int cnt, int first, int tile, cx<T>* part,
+                                                  int tid) {
+  constexpr int TY = GradTile<M>::Y, TX = GradTile<M>::X, GS = kGradZGroups, U = 8;
+  const int gi = tid >> 8, q = tid & 255, lane = tid & 63;
+  const int tpr = (n + TX - 1) / TX;
+  const int ty = (tile / tpr) * TY, tx = (tile % tpr) * TX;
+  const int y = ty + q / TX, x = tx + q % TX;
   const int per = (cnt + GS - 1) / GS, lo = min(cnt, gi * per), hi = min(cnt, lo + per);
   cx<T> acc{T(0), T(0)};
   for (int s0 = lo; s0 < hi; s0 += 64) {
     const int sj = s0 + lane;
     int2 p{0, 0};
-    if (sj < hi) p = g.pos[k0 + sj];
+    if (sj < hi) p = pos[sj];
     settle2(p);
-    const bool ov = sj < hi && !(p.x >= ty + TS || p.x + M <= ty || p.y >= tx + TS || p.y + M <= tx);
+    const bool ov = sj < hi && !(p.x >= ty + TY || p.x + M <= ty || p.y >= tx + TX || p.y + M <= tx);
     unsigned long long m = __ballot(ov);
     while (m != 0ull) {
       int sl[U], ox[U], oy[U];
@@ -1725,7 +1751,7 @@ __device__ __forceinline__ void grad_scatter_tile(const GradArgs& g, int k0, int
         if (u >= c) break;
         const int ry = y - ox[u], rx = x - oy[u];
         const bool in = (unsigned)ry < (unsigned)M && (unsigned)rx < (unsigned)M;
-        v[u] = in ? ldT<T>(g.gz_slots, (size_t)sl[u] * M * M + ry * M + rx) : cx<T>{T(0), T(0)};
+        v[u] = in ? ldT<T>(gz, (size_t)sl[u] * M * M + ry * M + rx) : cx<T>{T(0), T(0)};
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -1734,13 +1760,13 @@ __device__ __forceinline__ void grad_scatter_tile(const GradArgs& g, int k0, int
       }
     }
   }
-  if (gi > 0) part[(gi - 1) * TS * TS + q] = acc;
+  if (gi > 0) part[(gi - 1) * 256 + q] = acc;
   __syncthreads();
   if (gi == 0 && y < nr && x < n) {
 #pragma unroll
-    for (int k = 1; k < GS; ++k) acc = add(acc, part[(k - 1) * TS * TS + q]);
+    for (int k = 1; k < GS; ++k) acc = add(acc, part[(k - 1) * 256 + q]);
     const size_t o = (size_t)y * n + x;
-    stT<T>(g.gobj, o, first ? acc : add(ldT<T>(g.gobj, o), acc));
+    stT<T>(gobj, o, first ? acc : add(ldT<T>(gobj, o), acc));
   }
 }
 
@@ -1748,8 +1774,8 @@ __device__ __forceinline__ void grad_scatter_tile(const GradArgs& g, int k0, int
 // pattern groups (part: the unit's 256 partial sums; every thread of the block calls
 // this once, for the barrier)
 template <typename T, int M>
-__device__ __forceinline__ void grad_probe_unit(const GradArgs& g, int cnt, int first, int unit,
-                                                cx<T>* part, int tid) {  // cnt slots of probe sums
+__device__ __forceinline__ void grad_probe_unit(const cx<T>* gq, cx<T>* gprobe, int cnt, int first,
+                                                int unit, cx<T>* part, int tid) {  // cnt slots
   constexpr int G = kGradQGroups, PPU = 256 / G, U = 8;
   const int gi = tid / PPU, lp = tid % PPU;
   const int r = unit * PPU + lp;
@@ -1761,7 +1787,7 @@ __device__ __forceinline__ void grad_probe_unit(const GradArgs& g, int cnt, int 
       cx<T> v[U];
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        v[u] = s0 + u < hi ? ldT<T>(g.gq_slots, (size_t)(s0 + u) * M * M + r) : cx<T>{T(0), T(0)};
+        v[u] = s0 + u < hi ? ldT<T>(gq, (size_t)(s0 + u) * M * M + r) : cx<T>{T(0), T(0)};
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (s0 + u < hi) acc = add(acc, v[u]);
@@ -1773,32 +1799,50 @@ __device__ __forceinline__ void grad_probe_unit(const GradArgs& g, int cnt, int 
     cx<T> t = part[lp];
 #pragma unroll
     for (int k = 1; k < G; ++k) t = add(t, part[lp + k * PPU]);
-    stT<T>(g.gprobe, r, first ? t : add(ldT<T>(g.gprobe, r), t));
+    stT<T>(gprobe, r, first ? t : add(ldT<T>(gprobe, r), t));
   }
 }
 
 // the object and probe reductions of one chunk in one launch: blocks [0, tiles) take
-// object tiles, the others four probe units each (256 threads per unit)
+// object tiles, the next ones four probe units each (256 threads per unit), and one more
+// block adds the n_pos misfit terms where the total is wanted (a launch of its own for that
+// cost 400 patterns of 64^2 1.6 us of 25).  The slots stream from the caches: 3.6 TB/s at m = 128
 constexpr int kGradUnitsPerBlock = kGradZGroups;
-inline int grad_tiles(const GradArgs& g) {
-  return ((g.nr + kGradTile - 1) / kGradTile) * ((g.n + kGradTile - 1) / kGradTile);
+template <int M>
+int grad_tiles(const GradArgs& g) {
+  constexpr int Y = GradTile<M>::Y, X = GradTile<M>::X;
+  return ((g.nr + Y - 1) / Y) * ((g.n + X - 1) / X);
 }
-inline int grad_probe_blocks(int m) {
+__host__ __device__ constexpr int grad_probe_blocks(int m) {
   const int units = (m * m + 256 / kGradQGroups - 1) / (256 / kGradQGroups);
   return (units + kGradUnitsPerBlock - 1) / kGradUnitsPerBlock;
 }
 template <typename T, int M>
-__global__ __launch_bounds__(256 * kGradZGroups) void k_grad_reduce(GradArgs g, int k0, int cnt,
-                                                                     int probe_slots, int first,
-                                                                     int tiles) {
+__global__ __launch_bounds__(256 * kGradZGroups) void k_grad_reduce(
+    const int2* pos, const cx<T>* gz, const cx<T>* gq, int n, int cnt, int tiles, int probe_slots,
+    int nr, cx<T>* gobj, cx<T>* gprobe, int first, const double* phi, int n_pos, double* misfit) {
   __shared__ cx<T> part[256 * kGradZGroups];
-  const int tid = threadIdx.x;
-  if ((int)blockIdx.x < tiles)
-    grad_scatter_tile<T, M>(g, k0, cnt, first, blockIdx.x, part, tid);
-  else
-    grad_probe_unit<T, M>(g, probe_slots, first,
-                          ((int)blockIdx.x - tiles) * kGradUnitsPerBlock + (tid >> 8),
-                          part + (tid & ~255), tid & 255);
+  const int tid = threadIdx.x, blk = blockIdx.x, probe_blocks = grad_probe_blocks(M);
+  if (blk < tiles) {
+    grad_scatter_tile<T, M>(pos, gz, gobj, n, nr, cnt, first, blk, part, tid);
+  } else if (blk < tiles + probe_blocks) {
+    grad_probe_unit<T, M>(gq, gprobe, probe_slots, first,
+                          (blk - tiles) * kGradUnitsPerBlock + (tid >> 8), part + (tid & ~255),
+                          tid & 255);
+  } else if (tid < 256) {
+    sum_doubles(phi, n_pos, misfit, reinterpret_cast<double*>(part), tid);
+  }
+}
+template <typename T, int M>
+hipError_t launch_grad_reduce(const GradArgs& g, int k0, int cnt, int probe_slots, hipStream_t s) {
+  const int tiles = grad_tiles<M>(g);
+  const bool total = g.misfit && k0 + cnt == g.n_pos;
+  hipLaunchKernelGGL((k_grad_reduce<T, M>), dim3(tiles + grad_probe_blocks(M) + (total ? 1 : 0)),
+                     dim3(256 * kGradZGroups), 0, s, g.pos + k0, static_cast<const cx<T>*>(g.gz_slots),
+                     static_cast<const cx<T>*>(g.gq_slots), g.n, cnt, tiles, probe_slots, g.nr,
+                     static_cast<cx<T>*>(g.gobj), static_cast<cx<T>*>(g.gprobe), k0 == 0 ? 1 : 0,
+                     g.phi_all, g.n_pos, g.misfit);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -2134,17 +2178,13 @@ hipError_t Launchers<M>::chain(int v, int L, const StepArgs& a, int n_steps, con
 
 template <typename T, int M, int V>
 static hipError_t grad_t(const GradArgs& g, hipStream_t s) {
-  const int tiles = grad_tiles(g), blocks = tiles + grad_probe_blocks(M);
   for (int k0 = 0; k0 < g.n_pos; k0 += g.chunk) {
     const int cnt = min(g.chunk, g.n_pos - k0), groups = min(cnt, g.probe_slots);
-    const int first = k0 == 0;
     hipLaunchKernelGGL((k_grad_patch<T, M, V>), dim3(groups), dim3(GradPlan<T, M>::NT), 0, s, g.pos + k0,
                        static_cast<const cx<T>*>(g.obj), g.n, static_cast<const cx<T>*>(g.probe),
                        g.dperm + (size_t)k0 * M * M, static_cast<const cx<T>*>(g.tw), cnt,
                        static_cast<cx<T>*>(g.gz_slots), static_cast<cx<T>*>(g.gq_slots), g.phi_all + k0);
-    hipLaunchKernelGGL((k_grad_reduce<T, M>), dim3(blocks), dim3(256 * kGradZGroups), 0, s, g, k0,
-                       cnt, groups, first, tiles);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = launch_grad_reduce<T, M>(g, k0, cnt, groups, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

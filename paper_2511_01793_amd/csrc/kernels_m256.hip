@@ -424,7 +424,6 @@ hipError_t launch_grad256(const StepArgs& a, const GradArgs& g, hipStream_t s) {
   if (!a.part_q || g.chunk < 1) return hipErrorInvalidValue;
   StepArgs x = a;
   x.slot = nullptr;
-  const int tiles = grad_tiles(g), blocks = tiles + grad_probe_blocks(M);
   for (int k0 = 0; k0 < g.n_pos; k0 += g.chunk) {
     const int cnt = min(g.chunk, g.n_pos - k0);
     x.b = cnt;
@@ -435,15 +434,13 @@ hipError_t launch_grad256(const StepArgs& a, const GradArgs& g, hipStream_t s) {
     hipLaunchKernelGGL(k256_rows_grad, dim3(nsl * big::S), dim3(big::NT), 0, s, nsl, cnt, x.pos, x.stack,
                        x.tw, x.probe, x, k0, static_cast<float2*>(g.gz_slots),
                        static_cast<float2*>(g.gq_slots));
-    const int first = k0 == 0;
-    hipLaunchKernelGGL((k_grad_reduce<float, M>), dim3(blocks), dim3(256 * kGradZGroups), 0, s, g,
-                       k0, cnt, cnt, first, tiles);
-    const hipError_t e = hipGetLastError();
+    if (k0 + cnt == g.n_pos)  // the terms are complete: the last reduction adds them
+      hipLaunchKernelGGL(k256_phi_reduce, dim3((g.n_pos + 255) / 256), dim3(256), 0, s,
+                         (const double*)a.part_phi, g.n_pos, g.phi_all, 1.0 / (2.0 * M * M));
+    const hipError_t e = launch_grad_reduce<float, M>(g, k0, cnt, cnt, s);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k256_phi_reduce, dim3((g.n_pos + 255) / 256), dim3(256), 0, s,
-                     (const double*)a.part_phi, g.n_pos, g.phi_all, 1.0 / (2.0 * M * M));
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_check256(const StepArgs& a, int levels, int finalize_shape, double* out3,

@@ -157,6 +157,7 @@ struct GradArgs {
   void* gz_slots;      // chunk x m^2
   void* gq_slots;      // probe_slots x m^2
   double* phi_all;     // N
+  double* misfit;      // their sum, or null
 };
 hipError_t launch_grad(int m, int v, bool f64, const GradArgs& g, hipStream_t s);
 // patch-stage workgroups of the gradient at probe side m < 256 (k_grad_patch)
