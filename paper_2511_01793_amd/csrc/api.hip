@@ -133,6 +133,12 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // patterns in chunks of 32: 501 us, 64: 375, 128: 314, 256: 285.  The gradient also keeps two
 // slot buffers per chunk and is fastest at 128 (411 patterns: 24: 870 us, 64: 500, 128: 440, 256: 452).
 constexpr size_t kMisfitChunk256 = 256, kGradChunk256 = 128;
+// Patterns times pixels in a gradient chunk at m < 256 (128 MB of float32 slots).  A chunk has
+// two launches, and the second has the object's tiles to fill the chip with, however few
+// patterns reach them: 7000 patterns of 32^2 in chunks of 512: 292 us, 1024: 207, all at
+// once: 101; 6000 of 64^2 in chunks of 1024: 294 us, 4096: 255; 2310 of 128^2 in chunks of 512:
+// 500 us, 1024: 463, 2048: 472.
+constexpr size_t kGradChunkPixels = 16u << 20;
 size_t stack_slots(const emagpie_config& c) {
   const size_t B = (size_t)c.minibatch, N = (size_t)c.n_pos;
   return c.m == 256 ? std::max(B, std::min(N, kMisfitChunk256)) : B;
@@ -170,7 +176,7 @@ Layout make_layout(const emagpie_config& c) {
   L.scal = take(256);
   L.bar = take(256);
   L.phi_all = take(N * 8);
-  L.grad_chunk = (int)(c.m == 256 ? even_chunk(N, kGradChunk256) : std::min<size_t>(N, emg::kMaxSlots));
+  L.grad_chunk = (int)(c.m == 256 ? even_chunk(N, kGradChunk256) : std::min(N, kGradChunkPixels / m2));
   L.grad_probe_slots = c.m == 256 ? L.grad_chunk : std::min(L.grad_chunk, emg::grad_groups(c.m));
   const size_t gel = c.m <= 64 ? 16 : 8;  // complex128 where the float64 gradient exists
   L.gz = take((size_t)L.grad_chunk * m2 * gel);

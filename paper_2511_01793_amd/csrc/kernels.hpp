@@ -1692,10 +1692,11 @@ __device__ __forceinline__ void sum_doubles(const double* in, int count, double*
   if (tid == 0) out[0] = tot;
 }
 
-// Deterministic reductions of the per-pattern gradient slots.  Both split a
-// chunk's patterns into contiguous groups summed in parallel (ascending order
-// inside a group) and add the group partials in group order, with several loads
-// in flight per round; the order depends only on the chunk, not on the launch.
+// Deterministic reductions of the gradient slots.  Both split a chunk's slots into contiguous
+// groups summed in parallel and add the group partials in group order, with several loads in
+// flight per round; the order depends only on the chunk, not on the launch.  Inside a group
+// the object side sums 64 patterns at a time and the probe side 8 slots at a time, then adds
+// these sums: chains as short as those of chunks of 256, whatever the chunk.
 // Object gradient tiles of 256 pixels.  Rows of 256 bytes (32 columns) cross into fewer lines
 // that the next tile reads as well, square ones are reached by fewer patterns: 2310 patterns of
 // 128^2 463 us with 8 x 32 tiles, 477 us with 16 x 16; 300 of 32^2 18.2 and 16.2 us, 400 of 64^2
@@ -1723,8 +1724,9 @@ __device__ __forceinline__ void grad_scatter_tile(const int2* pos, const cx<T>* 
   const int ty = (tile / tpr) * TY, tx = (tile % tpr) * TX;
   const int y = ty + q / TX, x = tx + q % TX;
   const int per = (cnt + GS - 1) / GS, lo = min(cnt, gi * per), hi = min(cnt, lo + per);
-  cx<T> acc{T(0), T(0)};
+  cx<T> total{T(0), T(0)};
   for (int s0 = lo; s0 < hi; s0 += 64) {
+    cx<T> acc{T(0), T(0)};
     const int sj = s0 + lane;
     int2 p{0, 0};
     if (sj < hi) p = pos[sj];
@@ -1759,14 +1761,15 @@ __device__ __forceinline__ void grad_scatter_tile(const int2* pos, const cx<T>* 
         acc = add(acc, v[u]);
       }
     }
+    total = add(total, acc);
   }
-  if (gi > 0) part[(gi - 1) * 256 + q] = acc;
+  if (gi > 0) part[(gi - 1) * 256 + q] = total;
   __syncthreads();
   if (gi == 0 && y < nr && x < n) {
 #pragma unroll
-    for (int k = 1; k < GS; ++k) acc = add(acc, part[(k - 1) * 256 + q]);
+    for (int k = 1; k < GS; ++k) total = add(total, part[(k - 1) * 256 + q]);
     const size_t o = (size_t)y * n + x;
-    stT<T>(gobj, o, first ? acc : add(ldT<T>(gobj, o), acc));
+    stT<T>(gobj, o, first ? total : add(ldT<T>(gobj, o), total));
   }
 }
 
@@ -1788,9 +1791,11 @@ __device__ __forceinline__ void grad_probe_unit(const cx<T>* gq, cx<T>* gprobe, 
 #pragma unroll
       for (int u = 0; u < U; ++u)
         v[u] = s0 + u < hi ? ldT<T>(gq, (size_t)(s0 + u) * M * M + r) : cx<T>{T(0), T(0)};
+      cx<T> t = v[0];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (s0 + u < hi) acc = add(acc, v[u]);
+      for (int u = 1; u < U; ++u)
+        if (s0 + u < hi) t = add(t, v[u]);
+      acc = add(acc, t);
     }
   }
   part[tid] = acc;

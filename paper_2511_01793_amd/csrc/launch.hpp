@@ -6,7 +6,7 @@
 
 namespace emg {
 
-constexpr int kMaxSlots = 1024;  // patches per minibatch / gradient chunk
+constexpr int kMaxSlots = 1024;  // patches per minibatch
 
 struct StepArgs {
   // state (complex64, interleaved)
@@ -149,7 +149,7 @@ struct GradArgs {
   const float* dperm;
   const int2* pos;
   int n_pos;
-  int chunk;           // patterns per chunk (<= kMaxSlots)
+  int chunk;           // patterns per chunk
   const void* tw;      // twiddles in the gradient precision
   void* gobj;          // nr x n
   void* gprobe;        // m x m
