@@ -1228,6 +1228,7 @@ namespace {
 
 struct GroupClass {
   int m, L, v, f;  // probe side, levels, FFT plan, finalize shape
+  bool phase;      // some member has a zero-bin phase memory
   std::vector<int> inst;
   std::vector<size_t> patch_off, fin_off;  // per step: offset into the work arrays
   std::vector<int> patch_n, fin_n;         // per step: blocks
@@ -1264,10 +1265,11 @@ emagpie_status plan_group_cfgs(const std::vector<emagpie_config>& cfgs, GroupLay
     for (auto& k : G->classes)
       if (k.m == c.m && k.L == c.levels && k.v == c.fft_plan && k.f == c.finalize_shape) cls = &k;
     if (!cls) {
-      G->classes.push_back(GroupClass{c.m, c.levels, c.fft_plan, c.finalize_shape, {}, {}, {}, {}, {}});
+      G->classes.push_back(GroupClass{c.m, c.levels, c.fft_plan, c.finalize_shape, false, {}, {}, {}, {}, {}});
       cls = &G->classes.back();
     }
     cls->inst.push_back(i);
+    cls->phase = cls->phase || c.zero_phase_memory != 0;
   }
   G->work_host.clear();
   for (auto& k : G->classes) {
@@ -1491,7 +1493,7 @@ emagpie_status emagpie_group_epoch(emagpie_group g, void* const* obj_devs, void*
       ce = hipStreamWaitEvent(sc, g->fork_join[0], 0);
       for (int j = 0; ce == hipSuccess && j < J; ++j) {
         if (k.patch_n[j] > 0)
-          ce = emg::launch_patch_step_multi(k.m, k.v, k.L, g->args_dev, g->work_dev + k.patch_off[j],
+          ce = emg::launch_patch_step_multi(k.m, k.v, k.L, k.phase, g->args_dev, g->work_dev + k.patch_off[j],
                                             k.patch_n[j], sc);
         if (ce == hipSuccess && k.fin_n[j] > 0)
           ce = emg::launch_finalize_multi(k.m, k.f, g->args_dev, g->work_dev + k.fin_off[j], k.fin_n[j],

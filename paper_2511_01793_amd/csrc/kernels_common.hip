@@ -96,9 +96,9 @@ hipError_t launch_finalize(int m, int f, const StepArgs& a, hipStream_t s, hipEv
                            hipEvent_t e1) {
   EMG_BY_M(m, finalize(f, a, s, e0, e1));
 }
-hipError_t launch_patch_step_multi(int m, int v, int L, const StepArgs* args, const int2* work,
+hipError_t launch_patch_step_multi(int m, int v, int L, bool phase, const StepArgs* args, const int2* work,
                                    int blocks, hipStream_t s) {
-  EMG_BY_M(m, patch_step_multi(v, L, args, work, blocks, s));
+  EMG_BY_M(m, patch_step_multi(v, L, phase, args, work, blocks, s));
 }
 hipError_t launch_finalize_multi(int m, int f, const StepArgs* args, const int2* work, int blocks,
                                  hipStream_t s) {

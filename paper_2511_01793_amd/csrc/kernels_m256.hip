@@ -517,7 +517,7 @@ hipError_t Launchers256::persistent_grid_size(int, int, int, int* grid) {
 }
 
 // no m = 256 form (the host rejects these requests before they reach here)
-hipError_t Launchers256::patch_step_multi(int, int, const StepArgs*, const int2*, int, hipStream_t) {
+hipError_t Launchers256::patch_step_multi(int, int, bool, const StepArgs*, const int2*, int, hipStream_t) {
   return hipErrorInvalidValue;
 }
 hipError_t Launchers256::finalize_multi(int, const StepArgs*, const int2*, int, hipStream_t) {

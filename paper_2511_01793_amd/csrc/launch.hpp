@@ -55,7 +55,7 @@ hipError_t launch_finalize(int m, int f, const StepArgs& a, hipStream_t s, hipEv
                            hipEvent_t e1 = nullptr);
 // Many instances per launch: block b runs work[b] = (record in args, slot) for
 // the patch stage, or (record in args, finalize item) for the finalize.
-hipError_t launch_patch_step_multi(int m, int v, int L, const StepArgs* args, const int2* work,
+hipError_t launch_patch_step_multi(int m, int v, int L, bool phase, const StepArgs* args, const int2* work,
                                    int blocks, hipStream_t s);
 hipError_t launch_finalize_multi(int m, int f, const StepArgs* args, const int2* work, int blocks,
                                  hipStream_t s);
@@ -188,7 +188,7 @@ struct Launchers {
   static hipError_t patch_step(int v, int L, const StepArgs& a, hipStream_t s, hipEvent_t e0,
                                hipEvent_t e1);
   static hipError_t finalize(int f, const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
-  static hipError_t patch_step_multi(int v, int L, const StepArgs* args, const int2* work,
+  static hipError_t patch_step_multi(int v, int L, bool phase, const StepArgs* args, const int2* work,
                                      int blocks, hipStream_t s);
   static hipError_t finalize_multi(int f, const StepArgs* args, const int2* work, int blocks,
                                    hipStream_t s);
@@ -220,7 +220,7 @@ struct Launchers256 {
   static hipError_t patch_step(int v, int L, const StepArgs& a, hipStream_t s, hipEvent_t e0,
                                hipEvent_t e1);
   static hipError_t finalize(int f, const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
-  static hipError_t patch_step_multi(int v, int L, const StepArgs* args, const int2* work,
+  static hipError_t patch_step_multi(int v, int L, bool phase, const StepArgs* args, const int2* work,
                                      int blocks, hipStream_t s);
   static hipError_t finalize_multi(int f, const StepArgs* args, const int2* work, int blocks,
                                    hipStream_t s);
