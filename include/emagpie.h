@@ -239,7 +239,7 @@ emagpie_status emagpie_misfit(emagpie_ctx ctx, const void* obj_dev, const void* 
  * grad_obj = sum_k P_k^T conj(Q)(Q z_k - R_k) (n_rows x n_cols), grad_probe = sum_k
  * conj(z_k)(Q z_k - R_k) (m x m), and Phi to misfit_dev.  dtype EMAGPIE_F32
  * takes complex64 obj/probe/gradients (every m; at m = 256 the patterns go in
- * chunks of the minibatch through the row-strip and column-block kernels),
+ * chunks through the row-strip and column-block kernels),
  * EMAGPIE_F64 complex128 (m <= 64; EMAGPIE_E_UNSUPPORTED otherwise).  Gradients
  * are overwritten, not accumulated.
  */
