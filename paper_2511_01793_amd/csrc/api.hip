@@ -996,7 +996,7 @@ emagpie_status emagpie_step_minibatch(emagpie_ctx ctx, void* obj_dev, void* prob
   a.b = b;
   a.sampled = sampled_misfit_dev;
   if (ctx->cfg.path == EMAGPIE_PATH_CHAIN) {
-    EMG_HIP(emg::launch_chain_sweep(ctx->cfg.m, ctx->cfg.fft_plan, ctx->cfg.levels, a, b,
+    EMG_HIP(emg::launch_chain_sweep(ctx->cfg.m, ctx->cfg.fft_plan, ctx->cfg.levels, a, b, true,
                                     chain_sync(ctx), s));
     return EMAGPIE_OK;
   }
@@ -1065,7 +1065,7 @@ emagpie_status emagpie_epoch(emagpie_ctx ctx, void* obj_dev, void* probe_dev, in
       hipEvent_t e0, e1;
       EMG_OK(take_pair(ctx, 2, true, &e0, &e1));
       if (e0) EMG_HIP(hipEventRecord(e0, s));
-      EMG_HIP(emg::launch_chain_sweep(ctx->cfg.m, ctx->cfg.fft_plan, ctx->cfg.levels, a, N,
+      EMG_HIP(emg::launch_chain_sweep(ctx->cfg.m, ctx->cfg.fft_plan, ctx->cfg.levels, a, N, false,
                                       chain_sync(ctx), s));
       if (e1) EMG_HIP(hipEventRecord(e1, s));
       return EMAGPIE_OK;

@@ -2192,14 +2192,14 @@ hipError_t Launchers<M>::numerators(int v, int L, const StepArgs& a, hipStream_t
 }
 
 template <int M>
-hipError_t Launchers<M>::chain(int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
-                               hipStream_t s) {
+hipError_t Launchers<M>::chain(int v, int L, const StepArgs& a, int n_steps, bool add,
+                               const ChainSync& y, hipStream_t s) {
   return with_plan<M>(v, [&](auto vc) {
     return with_levels(L, [&](auto lc) {
       return with_phase(a, [&](auto pc) {
         constexpr int V = decltype(vc)::value, LV = decltype(lc)::value;
         constexpr bool PH = decltype(pc)::value;
-        const hipError_t e = launch_chain_clear(M, y.scratch, a.sampled, s);
+        const hipError_t e = launch_chain_clear(M, y.scratch, add ? nullptr : a.sampled, s);
         if (e != hipSuccess) return e;
         const int parties = Chain<M, V>::Workers + (a.sampled ? 1 : 0);
         hipLaunchKernelGGL((k_chain<M, V, LV, PH>), dim3(kDispatchXcds * (parties - 1) + 1),

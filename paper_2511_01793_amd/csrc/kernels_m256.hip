@@ -536,7 +536,7 @@ hipError_t Launchers256::revised_waves(int, const StepArgs&, hipStream_t) { retu
 hipError_t Launchers256::numerators(int, int, const StepArgs&, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t Launchers256::surrogate(int, const StepArgs&, double*, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t Launchers256::grad(int, bool, const GradArgs&, hipStream_t) { return hipErrorInvalidValue; }
-hipError_t Launchers256::chain(int, int, const StepArgs&, int, const ChainSync&, hipStream_t) {
+hipError_t Launchers256::chain(int, int, const StepArgs&, int, bool, const ChainSync&, hipStream_t) {
   return hipErrorInvalidValue;
 }
 

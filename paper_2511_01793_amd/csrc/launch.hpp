@@ -118,10 +118,10 @@ inline size_t chain_scratch_bytes(int m) {
 
 // One launch runs a whole sequential sweep (minibatch 1): a.slot points at n_steps
 // slots; each step's update is applied directly to the object window and the probe.
-// At m = 64 and 128 several workgroups share a step (kernels_chain.hpp).  y.scratch and
-// a.sampled are cleared on the stream first.
-hipError_t launch_chain_sweep(int m, int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
-                              hipStream_t s);
+// At m = 64 and 128 several workgroups share a step (kernels_chain.hpp).  y.scratch and, unless
+// the sweep's misfits are to be added to it (add), *a.sampled are cleared on the stream first.
+hipError_t launch_chain_sweep(int m, int v, int L, const StepArgs& a, int n_steps, bool add,
+                              const ChainSync& y, hipStream_t s);
 // its clearing of the scratch and of *sampled (nullable)
 hipError_t launch_chain_clear(int m, float2* scratch, double* sampled, hipStream_t s);
 
@@ -208,7 +208,7 @@ struct Launchers {
   static hipError_t numerators(int v, int L, const StepArgs& a, hipStream_t s);
   static hipError_t surrogate(int v, const StepArgs& a, double* terms, hipStream_t s);
   static hipError_t grad(int v, bool f64, const GradArgs& g, hipStream_t s);
-  static hipError_t chain(int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
+  static hipError_t chain(int v, int L, const StepArgs& a, int n_steps, bool add, const ChainSync& y,
                           hipStream_t s);
 };
 
@@ -240,7 +240,7 @@ struct Launchers256 {
   static hipError_t numerators(int v, int L, const StepArgs& a, hipStream_t s);
   static hipError_t surrogate(int v, const StepArgs& a, double* terms, hipStream_t s);
   static hipError_t grad(int v, bool f64, const GradArgs& g, hipStream_t s);
-  static hipError_t chain(int v, int L, const StepArgs& a, int n_steps, const ChainSync& y,
+  static hipError_t chain(int v, int L, const StepArgs& a, int n_steps, bool add, const ChainSync& y,
                           hipStream_t s);
 };
 
