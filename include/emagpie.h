@@ -22,8 +22,11 @@
  *    the host before anything is enqueued and leave all buffers untouched.
  *    emagpie_last_error(ctx) returns a message for the last failure of a
  *    call on that context (NULL: the last failure on the calling thread).
- *  - Device-side errors (workgroups of a persistent epoch or of a sequential
- *    sweep that gave up waiting for each other) are raised by the kernel into
+ *  - A sequential sweep shares its steps between workgroups only where all of them
+ *    have started; otherwise one workgroup does it (same results, slower), so no
+ *    other work on the device, of this or another process, makes it fail.
+ *  - Device-side errors (workgroups of a persistent epoch that gave up waiting
+ *    for each other, or of a sweep under fault injection) are raised by the kernel into
  *    host-visible memory and returned as EMAGPIE_E_HIP by the first call on the
  *    context made after the failing work has completed (synchronise the stream
  *    to be sure of seeing it); that call does nothing else, and the state the
@@ -65,7 +68,7 @@ enum {
   EMAGPIE_PATH_AUTO = 4, /* chosen at init by timing FUSED and GRAPH epochs (and
                             CHAIN when minibatch = 1); PERSISTENT only on request: a
                             cooperative launch slows the process's later launches   */
-  EMAGPIE_PATH_CHAIN = 5 /* minibatch 1 only: one launch runs the whole sequential
+  EMAGPIE_PATH_CHAIN = 5 /* minibatch 1 only: one kernel runs the whole sequential
                             sweep, each step applied in place (the paper's literal order,
                             Sec. 3 footnote: positions updated one after another)     */
 };
@@ -384,6 +387,14 @@ emagpie_status emagpie_misfit_noalloc(int32_t n_rows, int32_t n_cols, int32_t m,
  * Host only.
  */
 emagpie_status emagpie_debug_barrier(emagpie_ctx ctx, uint32_t spin_limit, uint32_t target_skew);
+
+/*
+ * Test hook of the sequential sweep: with absent = 1 later sweeps of ctx wait at their
+ * start for one workgroup more than is launched, so that every one of them gives the
+ * sharing up and runs in one workgroup (same results, slower).  0 restores normal use;
+ * EMAGPIE_E_ARG for other values.  Host only.
+ */
+emagpie_status emagpie_debug_chain(emagpie_ctx ctx, uint32_t absent);
 
 /*
  * Measured peaks for the roofline, on the caller's device buffer (bytes >=

@@ -281,6 +281,7 @@ struct emagpie_ctx_s {
   int* dev_err_dev = nullptr;
   unsigned spin_limit = kDefaultSpinLimit;
   unsigned bar_skew = 0;  // extra arrivals awaited (fault injection; 0 in normal use)
+  unsigned chain_absent = 0;  // workgroups a sequential sweep awaits that are not launched (likewise)
   std::string err;        // last failure of a call on this context
   // a context made by emagpie_init_many: its members and their group
   Many* many = nullptr;
@@ -364,7 +365,7 @@ emg::StepArgs base_args(emagpie_ctx c, void* obj, void* probe) {
 
 emg::ChainSync chain_sync(emagpie_ctx c) {
   return emg::ChainSync{reinterpret_cast<float2*>(c->ws + c->lay.chain.off), c->dev_err_dev,
-                        c->spin_limit, c->bar_skew};
+                        c->spin_limit, c->bar_skew, c->chain_absent};
 }
 
 // a (start, stop) event pair for timing category `cat`, or nulls when not timing
@@ -1636,6 +1637,14 @@ emagpie_status emagpie_debug_barrier(emagpie_ctx ctx, uint32_t spin_limit, uint3
   EMG_OK(use_ctx(ctx));
   ctx->spin_limit = spin_limit ? spin_limit : kDefaultSpinLimit;
   ctx->bar_skew = target_skew;
+  return EMAGPIE_OK;
+}
+
+emagpie_status emagpie_debug_chain(emagpie_ctx ctx, uint32_t absent) {
+  CtxErrScope es_(ctx);
+  EMG_OK(use_ctx(ctx));
+  if (absent > 1) return fail(EMAGPIE_E_ARG, "absent must be 0 or 1");
+  ctx->chain_absent = absent;
   return EMAGPIE_OK;
 }
 

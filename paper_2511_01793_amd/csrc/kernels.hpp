@@ -259,6 +259,16 @@ __device__ __forceinline__ float hw_rcp(float x) { return __builtin_amdgcn_rcpf(
 struct ToSlots {
   static constexpr bool direct = false;
 };
+struct InPlace {
+  static constexpr bool direct = true;
+  float2 *window, *probe_dev;
+  size_t n;  // object columns
+  int m;
+  __device__ __forceinline__ void object(int r, int c, cx<float> v, bool changed) const {
+    if (changed) st(window, (size_t)r * n + c, v);
+  }
+  __device__ __forceinline__ void probe(int r, int c, cx<float> v) const { st(probe_dev, (size_t)r * m + c, v); }
+};
 // ZP: the launch writes MAGPIE's z+ (a.zplus) instead of the numerators.
 // PART: what a direct sink gets, kObject | kProbe (the two have separate results).
 constexpr int kObject = 1, kProbe = 2;
@@ -506,8 +516,11 @@ __device__ __forceinline__ void xl_stage_amps(float* ampl, const float* ampv, in
 //
 // PH = false: the context keeps no phase memory (a.phase is null), and the
 // projection is compiled without it; PH = true tests a.phase at run time.
-template <int M, int V, int L, bool STAGE = false, bool PH = true>
-__device__ __forceinline__ void patch_step(const StepArgs& a, int s, cx<float>* A,
+//
+// SINK: a direct one (InPlace) applies the step instead of storing the slot's numerators; the
+// slot's sampled misfit is then returned in thread 0 and not stored.
+template <int M, int V, int L, bool STAGE = false, bool PH = true, class SINK = ToSlots>
+__device__ __forceinline__ double patch_step(const StepArgs& a, int s, cx<float>* A,
                                            cx<float>* tws, float* redf, double* redd,
                                            int tid) {
   using P = Px<M, V>;
@@ -727,28 +740,34 @@ __device__ __forceinline__ void patch_step(const StepArgs& a, int s, cx<float>* 
   }
   float qqmax, zmax;
   lds_max2<NT>(redf, qqmax, zmax);
-  pixel_update<M, V, L>(
-      a, s, tid,
-      [&](int rd, int r0, int c0, cx<float>* q, cx<float>* zz, cx<float>* Rv) {
+  auto values = [&](int rd, int r0, int c0, cx<float>* q, cx<float>* zz, cx<float>* Rv) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          if constexpr (P::CACHE) {
-            q[2 * i] = qc[2 * i];
-            q[2 * i + 1] = qc[2 * i + 1];
-            zz[2 * i] = zc[2 * i];
-            zz[2 * i + 1] = zc[2 * i + 1];
-          } else {
-            ld_pair(a.probe, (size_t)(r0 + i) * M + c0, q[2 * i], q[2 * i + 1]);
-            zz[2 * i] = ld(zwin, (size_t)(r0 + i) * n + c0);
-            zz[2 * i + 1] = ld(zwin, (size_t)(r0 + i) * n + c0 + 1);
-          }
-          Rv[2 * i] = A[at(r0 + i, c0)];
-          Rv[2 * i + 1] = A[at(r0 + i, c0 + 1)];
-        }
-      },
-      qqmax, zmax);
-  if (tid == 0 && a.phi) a.phi[s] = lds_sum<NT>(redd) / (2.0 * M * M);
+    for (int i = 0; i < 2; ++i) {
+      if constexpr (P::CACHE) {
+        q[2 * i] = qc[2 * i];
+        q[2 * i + 1] = qc[2 * i + 1];
+        zz[2 * i] = zc[2 * i];
+        zz[2 * i + 1] = zc[2 * i + 1];
+      } else {
+        ld_pair(a.probe, (size_t)(r0 + i) * M + c0, q[2 * i], q[2 * i + 1]);
+        zz[2 * i] = ld(zwin, (size_t)(r0 + i) * n + c0);
+        zz[2 * i + 1] = ld(zwin, (size_t)(r0 + i) * n + c0 + 1);
+      }
+      Rv[2 * i] = A[at(r0 + i, c0)];
+      Rv[2 * i + 1] = A[at(r0 + i, c0 + 1)];
+    }
+  };
+  double phi = 0.0;
+  if constexpr (SINK::direct) {
+    const SINK sink{a.obj + (size_t)sl.y * n + sl.z, a.probe, n, M};
+    pixel_update_body<M, PxLayout<M, V>, L, false>(a, s, tid, 0, values, qqmax, zmax, sink);
+    if (tid == 0) phi = lds_sum<NT>(redd) / (2.0 * M * M);
+  } else {
+    pixel_update<M, V, L>(a, s, tid, values, qqmax, zmax);
+    if (tid == 0 && a.phi) a.phi[s] = lds_sum<NT>(redd) / (2.0 * M * M);
+  }
   __syncthreads();  // LDS is reused by the next slot of a persistent loop
+  return phi;
 }
 
 // ---------------------------------------------------------------------------
@@ -2199,11 +2218,24 @@ hipError_t Launchers<M>::chain(int v, int L, const StepArgs& a, int n_steps, boo
       return with_phase(a, [&](auto pc) {
         constexpr int V = decltype(vc)::value, LV = decltype(lc)::value;
         constexpr bool PH = decltype(pc)::value;
+        const dim3 one(Plan<M, V>::NT);
+        if (n_steps < chain_min_steps(M, a.sampled != nullptr)) {
+          if (a.sampled && !add) {
+            const hipError_t e = launch_zero_doubles(a.sampled, 1, s);
+            if (e != hipSuccess) return e;
+          }
+          hipLaunchKernelGGL((k_sweep_one<M, V, LV, PH>), dim3(1), one, 0, s, a, n_steps,
+                             static_cast<const unsigned long long*>(nullptr));
+          return hipGetLastError();
+        }
         const hipError_t e = launch_chain_clear(M, y.scratch, add ? nullptr : a.sampled, s);
         if (e != hipSuccess) return e;
         const int parties = Chain<M, V>::Workers + (a.sampled ? 1 : 0);
         hipLaunchKernelGGL((k_chain<M, V, LV, PH>), dim3(kDispatchXcds * (parties - 1) + 1),
                            dim3(Chain<M, V>::NT), 0, s, a, n_steps, y);
+        if (parties > 1)
+          hipLaunchKernelGGL((k_sweep_one<M, V, LV, PH>), dim3(1), one, 0, s, a, n_steps,
+                             chain_roll(M, y.scratch));
         return hipGetLastError();
       });
     });

@@ -15,8 +15,16 @@
 // (a counter barrier of 16 workgroups with drained stores cost 1.5 us, three per step:
 // 8.7 us per step).  The workgroups are blocks 0, 8, 16, ... of the launch, which run on one
 // XCD and share its L2: the packets stay there (0.78 us per exchange of 16 workgroups, 4
-// packets per thread) and are read past the L1s.  Each workgroup checks the XCD of every other
-// at the start; where they differ the packets are written through to memory (1.5 us).
+// packets per thread) and are read past the L1s.  Where their XCDs differ the packets are
+// written through to memory (1.5 us).
+//
+// Waiting for each other's data is sound only among workgroups that are all running, and an
+// ordinary launch does not promise that: sweeps on several streams or of several processes, or
+// any other kernel, may hold the places.  So nobody waits for data before a roll call (roll_call)
+// has found every workgroup of the launch started.  Where that takes too long the first to
+// give up calls the sweep off for all: those started leave, those that start later leave at
+// once, nothing has been written, and k_sweep_one, launched behind, does the whole sweep in one
+// workgroup, which waits for nobody.  The decision is one atomic word's, so all take the same.
 //
 // A packet is overwritten one step later by its writer, which by then has received data that
 // every reader sends only after reading it (each phase needs data of all workgroups
@@ -76,6 +84,32 @@ struct ChainWait {
       if (give_up(polls)) break;
   }
 };
+
+// Roll call of a launch, one word: six bits per XCD with the workers that started there, from
+// bit kRollCount the workgroups that started, and kRollOff once one has given up on the others.
+constexpr int kRollXcdBits = 6, kRollCount = 54;
+constexpr unsigned long long kRollOff = 1ull << 63;
+// Looks at the word before giving up, each about a microsecond: some milliseconds, more than
+// the tail of a kernel that is making room.
+constexpr unsigned kRollPolls = 1u << 12;
+__device__ __forceinline__ void roll_answer(unsigned long long* word, bool worker, unsigned xcd) {
+  const unsigned long long place = worker && xcd < kDispatchXcds ? 1ull << (kRollXcdBits * xcd) : 0ull;
+  (void)__hip_atomic_fetch_add(word, (1ull << kRollCount) + place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// the word with all `parties` started, or with kRollOff: which of the two comes first is final
+__device__ __forceinline__ unsigned long long roll_call(unsigned long long* word, unsigned parties) {
+  unsigned long long w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (unsigned polls = 0; !(w & kRollOff) && (unsigned)(w >> kRollCount) < parties; ++polls) {
+    if (polls < kRollPolls) {
+      __builtin_amdgcn_s_sleep(1);
+      w = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (__hip_atomic_compare_exchange_strong(word, &w, w | kRollOff, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT)) {
+      w |= kRollOff;
+    }  // else another has started or given up meanwhile, and w is the word now
+  }
+  return w;
+}
 
 typedef int chain_packet __attribute__((ext_vector_type(4)));
 // N packets; shared_l2: every reader is on this XCD, so the packets may stay in its L2
@@ -319,23 +353,33 @@ __global__ __launch_bounds__((Chain<M, V>::NT)) void k_chain(StepArgs a, int n_s
   __shared__ alignas(16) cx<float> Q[LINES * LS], Z2[(SOLO ? 2 : 1) * LINES * LS], W[LINES * LS];
   __shared__ float redf[2 * NT / 64];
   __shared__ int dead;
+  __shared__ unsigned long long rolled;
   if (blockIdx.x % kDispatchXcds != 0) return;
   const int tid = threadIdx.x, ln = tid & 63, party = blockIdx.x / kDispatchXcds;
-  if (tid == 0) dead = 0;
+  const unsigned parties = C::Workers + (a.sampled ? 1 : 0);
+  unsigned long long* roll = reinterpret_cast<unsigned long long*>(y.scratch + 2 * chain_clear_units(M)) - 1;
+  const unsigned xcd = __builtin_amdgcn_s_getreg(kHwRegXccId) & 15u;
+  if (tid == 0) {
+    dead = 0;
+    if (parties > 1) roll_answer(roll, party < C::Workers, xcd);
+  }
   const ChainWait wait{y.spin_limit, y.err, &dead};
   // the scratch in packets: the tile after the row and after the column phase, the
-  // new window, the maxima, the XCD numbers, the counters, the terms
+  // new window, the maxima, the counters, the terms
   float2* tile1 = y.scratch;
   float2 *tile2 = tile1 + 2 * M * M, *window = tile2 + 2 * M * M, *maxima = window + 2 * M * M;
-  unsigned* counters = reinterpret_cast<unsigned*>(maxima + 2 * 64 + 2 * 32);
+  unsigned* counters = reinterpret_cast<unsigned*>(maxima + 2 * 64);
   constexpr size_t kTermsAt = 2 * chain_clear_units(M);
   float* terms = reinterpret_cast<float*>(y.scratch + kTermsAt);
   if (party == C::Workers) {
+    if (tid == 0) rolled = roll_call(roll, parties + y.absent);
+    __syncthreads();
+    if (rolled & kRollOff) return;
     chain_account<M, V>(a, n_steps, terms, counters, wait, y.skew);
     return;
   }
   const __amdgpu_buffer_rsrc_t b1 = through_buffer(tile1, 2 * M * M), b2 = through_buffer(tile2, 2 * M * M),
-                               bw = through_buffer(window, 2 * M * M), bm = through_buffer(maxima, 2 * 64), bx = through_buffer(maxima + 2 * 64, 2 * 32),
+                               bw = through_buffer(window, 2 * M * M), bm = through_buffer(maxima, 2 * 64),
                                cb = through_buffer(reinterpret_cast<float2*>(counters), 32);
   const int line0 = party * LINES;  // its rows, and columns
   // places in the passes.  Strided row passes: lanes of a row beside each other (window
@@ -435,16 +479,16 @@ __global__ __launch_bounds__((Chain<M, V>::NT)) void k_chain(StepArgs a, int n_s
   cx<float> z[4];
   load_window(sl, z);
   load_intensities(sl.x);
+  if (parties > 1 && tid == 0) rolled = roll_call(roll, parties + y.absent);
   __syncthreads();
-  // are all workgroups on one XCD?  Each tells its XCD's number and looks at every other's.
+  // all workers on this one's XCD
   bool shared_l2 = false;
-  if constexpr (!SOLO) {
-    const float xcd = (float)(__builtin_amdgcn_s_getreg(kHwRegXccId) & 15u);
-    const int to = party, from = ln % C::Workers;
-    cx<float> m{xcd, 0.f};
-    if (tid == 0) send<1>(bx, &to, &m, 1u, false);
-    receive<1>(bx, &from, every, &m, 1u + y.skew, wait);
-    shared_l2 = __ballot(m.re != xcd) == 0ull;
+  if (parties > 1) {
+    const unsigned long long w = rolled;
+    if (w & kRollOff) return;
+    shared_l2 = xcd < kDispatchXcds &&
+                (int)((w >> (kRollXcdBits * (xcd % kDispatchXcds))) & ((1 << kRollXcdBits) - 1)) == C::Workers;
+    shared_l2 = __builtin_amdgcn_readfirstlane(shared_l2);
   }
 
   for (int step = 0; step < n_steps; ++step) {
@@ -638,6 +682,33 @@ __global__ __launch_bounds__((Chain<M, V>::NT)) void k_chain(StepArgs a, int n_s
     __hip_atomic_fetch_add(counters + kChainStored, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (a.update_probe)
     for (int e = tid; e < LINES * M; e += NT) st(a.probe, (size_t)line0 * M + e, Q[(e / M) * LS + e % M]);
+}
+
+// The sweep in one workgroup: of few steps, or (roll) one that the launch before called off.
+// Every step touches only its own window and the probe, and the workgroup barrier at its end
+// orders it before the next.  3.8 us per step at m = 32, 8 at m = 64, 28 at m = 128.
+template <int M, int V, int L, bool PH>
+__global__ __launch_bounds__((Plan<M, V>::NT)) void k_sweep_one(StepArgs a, int n_steps,
+                                                               const unsigned long long* roll) {
+  __shared__ cx<float> A[M * lds_stride<M>()];
+  __shared__ cx<float> tws[M];
+  __shared__ float redf[32];
+  __shared__ double redd[16];
+  if (roll && !(*roll & kRollOff)) return;
+  const int tid = threadIdx.x;
+  stage_twiddles<M, Plan<M, V>::NT>(a.tw, tws, tid);
+  __syncthreads();
+  // the finalize's additions
+  double sampled = (tid == 0 && a.sampled) ? *a.sampled : 0.0;
+  for (int step = 0; step < n_steps; ++step) {
+    StepArgs x = a;
+    x.slot = a.slot + step;
+    x.b = 1;
+    double t = 0.0;
+    t += patch_step<M, V, L, false, PH, InPlace>(x, 0, A, tws, redf, redd, tid);
+    sampled += t;
+  }
+  if (tid == 0 && a.sampled) *a.sampled = sampled;
 }
 
 }  // namespace emg

@@ -104,13 +104,25 @@ struct ChainSync {
   int* err;             // device-visible error flag, set when a wait gives up
   unsigned spin_limit;  // polls of one wait before it gives up
   unsigned skew;        // added to the sequence numbers awaited (fault injection; 0 in normal use)
+  unsigned absent;      // added to the workgroups awaited at the start (likewise)
 };
 // Scratch layout, in 16-byte units: two copies of the tile and the updated window, m^2
-// each; the maxima of every wave; the workgroups' XCDs; the counters; then (not cleared) the misfit terms of the
+// each; the maxima of every wave; the counters; then (not cleared) the misfit terms of the
 // last kChainTermSteps steps, m^2 floats each.  None for the probe sides without it.
 constexpr int kChainTermSteps = 4;
 constexpr int kChainCounterUnits = 16;
-constexpr size_t chain_clear_units(int m) { return 3 * (size_t)m * m + 64 + 32 + kChainCounterUnits; }
+constexpr size_t chain_clear_units(int m) { return 3 * (size_t)m * m + 64 + kChainCounterUnits; }
+// the roll call's word: the last of the counters
+inline unsigned long long* chain_roll(int m, float2* scratch) {
+  return reinterpret_cast<unsigned long long*>(scratch + 2 * chain_clear_units(m)) - 1;
+}
+// Sweeps of fewer steps run in one workgroup from the start, without the clearing, the roll call
+// and the launch behind.  Microseconds per sweep, one workgroup and shared: m = 32 16 steps 71.6
+// and 74.5, 32 steps 131.8 and 131.4 (without the sampled misfit 12: 52.4 and 53.8, 16: 67.5 and
+// 67.7); m = 64 2 steps 27.2 and 29.0, 3 steps 35.2 and 34.8; m = 128 1 step 41.3 and 27.3.
+constexpr int chain_min_steps(int m, bool sampled) {
+  return m == 32 ? (sampled ? 32 : 16) : m == 64 ? 3 : 1;
+}
 inline size_t chain_scratch_bytes(int m) {
   if (m > 128) return 0;  // no sequential sweep
   return chain_clear_units(m) * 16 + (size_t)kChainTermSteps * m * m * 4;
@@ -118,7 +130,8 @@ inline size_t chain_scratch_bytes(int m) {
 
 // One launch runs a whole sequential sweep (minibatch 1): a.slot points at n_steps
 // slots; each step's update is applied directly to the object window and the probe.
-// At m = 64 and 128 several workgroups share a step (kernels_chain.hpp).  y.scratch and, unless
+// Several workgroups share the sweep (kernels_chain.hpp); where they do not get to run together,
+// the kernel launched after them does it in one.  y.scratch and, unless
 // the sweep's misfits are to be added to it (add), *a.sampled are cleared on the stream first.
 hipError_t launch_chain_sweep(int m, int v, int L, const StepArgs& a, int n_steps, bool add,
                               const ChainSync& y, hipStream_t s);

@@ -34,7 +34,7 @@ EXPORTS = [
     "emagpie_group_workspace_size", "emagpie_group_create", "emagpie_group_epoch",
     "emagpie_group_destroy", "emagpie_plan_get", "emagpie_plan_describe", "emagpie_check_step",
     "emagpie_phase_memory_reset", "emagpie_workspace_size_many", "emagpie_init_many",
-    "emagpie_epoch_many", "emagpie_many_member", "emagpie_debug_barrier", "emagpie_measure_peaks",
+    "emagpie_epoch_many", "emagpie_many_member", "emagpie_debug_barrier", "emagpie_debug_chain", "emagpie_measure_peaks",
     "emagpie_misfit_noalloc",
 ]
 
@@ -120,6 +120,7 @@ def lib() -> ctypes.CDLL:
         "emagpie_epoch_many": [vp, vp, vp, i64, vp, vp],
         "emagpie_many_member": [vp, i32, ctypes.POINTER(vp)],
         "emagpie_debug_barrier": [vp, ctypes.c_uint32, ctypes.c_uint32],
+        "emagpie_debug_chain": [vp, ctypes.c_uint32],
         "emagpie_measure_peaks": [vp, sz, i32, vp, vp],
         "emagpie_misfit_noalloc": [i32, i32, i32, i32, vp, vp, vp, vp, vp, vp],
     }
@@ -305,6 +306,11 @@ class Reconstruction:
         wait for target_skew extra arrivals, so with target_skew > 0 every wait gives up and
         the next call raises E_HIP."""
         _check(lib().emagpie_debug_barrier(self._ctx, int(spin_limit), int(target_skew)), self._ctx)
+
+    def debug_chain(self, absent: bool = False):
+        """Test hook: with absent, later sequential sweeps wait for a workgroup that is not
+        launched, give the sharing up and run in one workgroup (same results)."""
+        _check(lib().emagpie_debug_chain(self._ctx, int(bool(absent))), self._ctx)
 
     @property
     def last_error(self) -> str:
