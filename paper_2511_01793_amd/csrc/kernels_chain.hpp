@@ -588,7 +588,11 @@ __global__ __launch_bounds__((Chain<M, V>::NT)) void k_chain(StepArgs a, int n_s
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (dead) break;
+    // `dead` is looked at where no wave can set it between this barrier and the next, so that
+    // all waves see the same: here, or where one workgroup has no barrier before its wait for
+    // the summing one below, after the barrier that follows that
+    if constexpr (!SOLO)
+      if (dead) break;
     if (a.sampled && tid == 0 && step > 0)
       __hip_atomic_fetch_add(counters + kChainStored, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     get_contiguous(in_column, v);
@@ -627,6 +631,7 @@ __global__ __launch_bounds__((Chain<M, V>::NT)) void k_chain(StepArgs a, int n_s
     float qqmax, zmax;
     if constexpr (SOLO) {
       __syncthreads();
+      if (dead) break;
       get_contiguous(in_row, v);
       group_dft<R1, true>(v, ct);
       lds_max2<NT>(redf, qqmax, zmax);

@@ -118,3 +118,33 @@ def test_captured_sweep_is_decided_at_each_replay(absent):
         (obj.abs().sum() + probe.abs().sum()).item()
     del g
     rec.close()
+
+
+@pytest.mark.parametrize("m, absent", [(32, False), (64, False), (64, True)])
+def test_given_up_waits_leave_the_sweep_together(m, absent):
+    """Waits made to give up end the launch normally and are reported once; a sweep that is called
+    off has no such wait.  The context works afterwards."""
+    print("case: chain give up", m, absent, flush=True)
+    p = small(m, 6)
+    rec = rec_for(p, "chain")
+    rec.debug_barrier(100, 1)
+    rec.debug_chain(absent)
+    obj, probe = init_state(p, rec)
+    s = torch.zeros((), dtype=torch.float64, device="cuda")
+    rec.epoch(obj, probe, 0, sampled=s)
+    torch.cuda.synchronize()
+    if not absent:
+        with pytest.raises(E.EmagpieError) as err:
+            rec.debug_barrier(0, 0)
+        assert err.value.name == "E_HIP"
+    rec.debug_barrier(0, 0)
+    rec.debug_chain(False)
+    obj, probe = init_state(p, rec)
+    totals = []
+    for e in range(2):
+        s = torch.zeros((), dtype=torch.float64, device="cuda")
+        rec.epoch(obj, probe, e, sampled=s)
+        totals.append(s)
+    torch.cuda.synchronize()
+    rec.close()
+    same((obj, probe, [float(x.item()) for x in totals]), sweeps(p, "fused"))
