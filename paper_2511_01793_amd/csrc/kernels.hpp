@@ -1719,13 +1719,14 @@ __global__ __launch_bounds__((GradPlan<T, M>::NT)) void k_grad_patch(const int2*
   }
 }
 
-// sum of `count` doubles by 256 threads (redd: 16 doubles): thread t adds in[t],
-// in[t + 256], ... in that order; eight loads in flight per round
+// sum of `count` doubles by the first 256 threads (redd: 16 doubles): thread t adds in[t],
+// in[t + 256], ... in that order; eight loads in flight per round.  Every thread of a larger
+// block calls it, for the barriers.
 __device__ __forceinline__ void sum_doubles(const double* in, int count, double* out, double* redd,
                                             int tid) {
   constexpr int U = 8;
   double acc = 0.0;
-  for (int i0 = tid; i0 < count; i0 += 256 * U) {
+  for (int i0 = tid < 256 ? tid : count; i0 < count; i0 += 256 * U) {
     double v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = i0 + 256 * u < count ? in[i0 + 256 * u] : 0.0;
@@ -1879,7 +1880,7 @@ __global__ __launch_bounds__(256 * kGradZGroups) void k_grad_reduce(
     grad_probe_unit<T, M>(gq, gprobe, probe_slots, first,
                           (blk - tiles) * kGradUnitsPerBlock + (tid >> 8), part + (tid & ~255),
                           tid & 255);
-  } else if (tid < 256) {
+  } else {
     sum_doubles(phi, n_pos, misfit, reinterpret_cast<double*>(part), tid);
   }
 }
