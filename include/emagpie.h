@@ -144,8 +144,8 @@ emagpie_status emagpie_workspace_size(const emagpie_config* cfg, size_t* bytes);
  * returns EMAGPIE_E_DATA if any intensity is NaN or Inf.
  *
  * Autotuning (fft_plan or finalize_shape = EMAGPIE_TUNE, or path =
- * EMAGPIE_PATH_AUTO): unless tune_cache holds a result for this device and
- * problem shape, init times the candidates on the given intensities and
+ * EMAGPIE_PATH_AUTO): unless tune_cache holds a result for this device,
+ * problem shape and build of the library's kernels, init times the candidates on the given intensities and
  * positions with a scratch state held in the workspace: each FFT plan's
  * patch-stage kernel and each finalize shape over minibatches of the epoch-0
  * scan order, then whole epochs of each candidate path (fused and graph, and

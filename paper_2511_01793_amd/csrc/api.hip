@@ -443,6 +443,13 @@ void fill_plan_info(emagpie_ctx c, int tuned) {
   }
 }
 
+// the sources this library was built from (build.py)
+#ifndef EMG_SOURCE_TAG
+#define EMG_SOURCE_TAG "untagged"
+#endif
+
+// Device, problem and options of a tuning result, and the kernels that were timed: a record of
+// another build's does not match.
 std::string tune_key(emagpie_ctx c, const emagpie_config& req) {
   hipDeviceProp_t prop{};
   int dev = 0;
@@ -454,7 +461,7 @@ std::string tune_key(emagpie_ctx c, const emagpie_config& req) {
   const emagpie_config& k = c->cfg;
   char buf[512];
   std::snprintf(buf, sizeof buf,
-                "%s cus=%d m=%d n=%dx%d N=%d B=%d L=%d blind=%d joint=%d az1=%d mem=%d plan=%d "
+                "%s cus=%d kernels=" EMG_SOURCE_TAG " m=%d n=%dx%d N=%d B=%d L=%d blind=%d joint=%d az1=%d mem=%d plan=%d "
                 "shape=%d path=%d",
                 arch.c_str(), c->num_cus, k.m, k.n_rows, k.n_cols, k.n_pos, k.minibatch, k.levels, k.update_probe,
                 k.joint_step, k.alpha_z == 1.0f ? 1 : 0, k.zero_phase_memory, req.fft_plan,

@@ -5,6 +5,7 @@ Usage: python -m paper_2511_01793_amd.csrc.build   (or call build()).
 from __future__ import annotations
 
 import concurrent.futures
+import hashlib
 import os
 import shutil
 import subprocess
@@ -47,12 +48,26 @@ def _run(cmd):
     return r
 
 
+def source_tag(here: str = HERE, header: str = os.path.join(ROOT, "include", "emagpie.h")) -> str:
+    """Names the kernels a library is built from: a hash of the sources, headers and flags.  It is part
+    of the key of a tuning record, whose times hold for the kernels that were timed."""
+    h = hashlib.sha256(" ".join(f for f in HIPFLAGS if not f.startswith("-I")).encode())
+    names = sorted(SOURCES + [f for f in os.listdir(here) if f.endswith(".hpp")])
+    for path in [os.path.join(here, f) for f in names] + [header]:
+        with open(path, "rb") as f:
+            data = f.read()
+        h.update(f"{os.path.basename(path)} {len(data)} ".encode() + data)
+    return h.hexdigest()[:16]
+
+
 def build(verbose: bool = False) -> str:
     hipcc = _hipcc()
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     objs = [os.path.join(objdir, os.path.splitext(s)[0] + ".o") for s in SOURCES]
-    cmds = [[hipcc, *HIPFLAGS, "-c", os.path.join(HERE, s), "-o", o] for s, o in zip(SOURCES, objs)]
+    tag = {"api.hip": [f'-DEMG_SOURCE_TAG="{source_tag()}"']}
+    cmds = [[hipcc, *HIPFLAGS, *tag.get(s, []), "-c", os.path.join(HERE, s), "-o", o]
+            for s, o in zip(SOURCES, objs)]
     with concurrent.futures.ThreadPoolExecutor(max_workers=len(cmds)) as ex:
         for r in ex.map(_run, cmds):
             if verbose:
