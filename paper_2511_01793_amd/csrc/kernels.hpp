@@ -2229,9 +2229,11 @@ hipError_t Launchers<M>::chain(int v, int L, const StepArgs& a, int n_steps, boo
                              static_cast<const unsigned long long*>(nullptr));
           return hipGetLastError();
         }
-        const hipError_t e = launch_chain_clear(M, y.scratch, add ? nullptr : a.sampled, s);
-        if (e != hipSuccess) return e;
         const int parties = Chain<M, V>::Workers + (a.sampled ? 1 : 0);
+        if (parties > 1) {  // one alone exchanges nothing
+          const hipError_t e = launch_chain_clear(M, y.scratch, add ? nullptr : a.sampled, s);
+          if (e != hipSuccess) return e;
+        }
         hipLaunchKernelGGL((k_chain<M, V, LV, PH>), dim3(kDispatchXcds * (parties - 1) + 1),
                            dim3(Chain<M, V>::NT), 0, s, a, n_steps, y);
         if (parties > 1)

@@ -36,7 +36,8 @@ __global__ __launch_bounds__(256) void k_fill_c64(float2* p, size_t count, float
 }
 
 // No sequence number of an earlier launch may be found in the scratch (a captured launch is
-// replayed with the same numbers).  One workgroup alone (m = 32) uses only the counters.
+// replayed with the same numbers).  The one worker of m = 32 and its summing workgroup use only
+// the counters.
 __global__ __launch_bounds__(256) void k_chain_clear(float4* p, int count, double* sampled) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < count) p[i] = make_float4(0.f, 0.f, 0.f, 0.f);

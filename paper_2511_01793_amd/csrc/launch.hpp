@@ -118,10 +118,11 @@ inline unsigned long long* chain_roll(int m, float2* scratch) {
 }
 // Sweeps of fewer steps run in one workgroup from the start, without the clearing, the roll call
 // and the launch behind.  Microseconds per sweep, one workgroup and shared: m = 32 16 steps 71.6
-// and 74.5, 32 steps 131.8 and 131.4 (without the sampled misfit 12: 52.4 and 53.8, 16: 67.5 and
-// 67.7); m = 64 2 steps 27.2 and 29.0, 3 steps 35.2 and 34.8; m = 128 1 step 41.3 and 27.3.
+// and 74.5, 32 steps 131.8 and 131.4; m = 64 2 steps 27.2 and 29.0, 3 steps 35.2 and 34.8; m = 128
+// 1 step 41.3 and 27.3.  m = 32 without the sampled misfit has one workgroup, and none of the
+// three, either way: 4 steps 22.0 and 21.5, 16 steps 67.4 and 63.7.
 constexpr int chain_min_steps(int m, bool sampled) {
-  return m == 32 ? (sampled ? 32 : 16) : m == 64 ? 3 : 1;
+  return m == 32 && sampled ? 32 : m == 64 ? 3 : 1;
 }
 inline size_t chain_scratch_bytes(int m) {
   if (m > 128) return 0;  // no sequential sweep

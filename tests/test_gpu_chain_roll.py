@@ -148,3 +148,22 @@ def test_given_up_waits_leave_the_sweep_together(m, absent):
     torch.cuda.synchronize()
     rec.close()
     same((obj, probe, [float(x.item()) for x in totals]), sweeps(p, "fused"))
+
+
+def test_a_worker_alone_leaves_the_scratch_as_it_is():
+    """m = 32 without the sampled misfit is one workgroup's work: nothing is exchanged, and nothing cleared
+    for it (the exchange scratch is the end of the workspace)."""
+    print("case: chain without scratch", flush=True)
+    p = small(32, 6)
+    rec = rec_for(p, "chain")
+    obj, probe = init_state(p, rec)
+    end = rec._ws_ptr - rec._ws.data_ptr() + E.workspace_size(rec.cfg)
+    scratch = rec._ws[end - (64 << 10):end]
+    scratch.fill_(0x5A)
+    rec.epoch(obj, probe, 0)
+    torch.cuda.synchronize()
+    assert bool((scratch == 0x5A).all())
+    rec.epoch(obj, probe, 1, sampled=torch.zeros((), dtype=torch.float64, device="cuda"))
+    torch.cuda.synchronize()
+    assert not bool((scratch == 0x5A).all())
+    rec.close()
