@@ -129,7 +129,13 @@ typedef struct {
                             where not timed (PLAIN is never a candidate)            */
 } emagpie_plan;
 
-/* Bytes of device workspace a context with this configuration needs. */
+/*
+ * Bytes of device workspace a context with this configuration needs.  The largest parts are
+ * the copy of the intensities (n_pos m^2 floats); the minibatch's numerators (about 20 bytes
+ * per pixel of every pattern of it); and, for every context, whether it takes gradients or not,
+ * the gradient's slots: 8 bytes (m <= 64: 16) per pixel of every pattern up to 128 MiB and at
+ * most 32 MiB for the probe (64 MiB at m = 256, whose first part is the misfit's buffer too).
+ */
 emagpie_status emagpie_workspace_size(const emagpie_config* cfg, size_t* bytes);
 
 /*

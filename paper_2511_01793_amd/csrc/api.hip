@@ -121,7 +121,7 @@ bool wants_tuning(const emagpie_config& c) {
 struct Layout {
   Region dperm, pos, slots, morder, tw32, tw64, numer, pnum, pden, pden_slot, phi, stack, zmax, ubuf, Dbuf,
       scal, bar, phi_all, gz, gq, tune_obj, tune_probe, phase, part, chain;
-  int grad_chunk, grad_probe_slots;
+  int grad_chunk, grad_chunk64, grad_probe_slots;  // patterns per chunk in float32 and in float64
   size_t total;
 };
 
@@ -131,22 +131,25 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // gradient run through it in chunks too, up to 256 (128 MB, half of the Infinity Cache).
 // Chunks of a minibatch left most of the chip idle between launches; full misfit of 961
 // patterns in chunks of 32: 501 us, 64: 375, 128: 314, 256: 285.  The gradient also keeps two
-// slot buffers per chunk and is fastest at 128 (411 patterns: 24: 870 us, 64: 500, 128: 440, 256: 452).
+// slot buffers per chunk and is fastest at 128 (411 patterns: 24: 870 us, 64: 500, 128: 440, 256: 452);
+// its object slots take the tiles behind its chunk's.
 constexpr size_t kMisfitChunk256 = 256, kGradChunk256 = 128;
-// Patterns times pixels in a gradient chunk at m < 256 (128 MB of float32 slots).  A chunk has
+// Patterns times pixels in a float32 gradient chunk at m < 256 (128 MB of slots; a float64 chunk
+// has half as many in the same memory).  A chunk has
 // two launches, and the second has the object's tiles to fill the chip with, however few
 // patterns reach them: 7000 patterns of 32^2 in chunks of 512: 292 us, 1024: 207, all at
 // once: 101; 6000 of 64^2 in chunks of 1024: 294 us, 4096: 255; 2310 of 128^2 in chunks of 512:
-// 500 us, 1024: 463, 2048: 472.
+// 500 us, 1024: 463, 2048: 472.  In float64 half a chunk against a whole one: 3000 patterns of 64^2
+// 246 and 234 us, 4000: 313 and 332, 6000: 464 and 496; 10000 of 32^2 242 and 237.
 constexpr size_t kGradChunkPixels = 16u << 20;
-size_t stack_slots(const emagpie_config& c) {
-  const size_t B = (size_t)c.minibatch, N = (size_t)c.n_pos;
-  return c.m == 256 ? std::max(B, std::min(N, kMisfitChunk256)) : B;
-}
 // patterns per chunk when n are taken in as few chunks of at most `most` as there have to be
 size_t even_chunk(size_t n, size_t most) {
   const size_t chunks = (n + most - 1) / most;
   return (n + chunks - 1) / chunks;
+}
+size_t stack_slots(const emagpie_config& c) {
+  const size_t B = (size_t)c.minibatch, N = (size_t)c.n_pos;
+  return c.m == 256 ? std::max({B, std::min(N, kMisfitChunk256), 2 * even_chunk(N, kGradChunk256)}) : B;
 }
 
 Layout make_layout(const emagpie_config& c) {
@@ -177,10 +180,11 @@ Layout make_layout(const emagpie_config& c) {
   L.bar = take(256);
   L.phi_all = take(N * 8);
   L.grad_chunk = (int)(c.m == 256 ? even_chunk(N, kGradChunk256) : std::min(N, kGradChunkPixels / m2));
+  L.grad_chunk64 = c.m <= 64 ? (int)even_chunk(N, kGradChunkPixels / 2 / m2) : 0;  // where it exists
   L.grad_probe_slots = c.m == 256 ? L.grad_chunk : std::min(L.grad_chunk, emg::grad_groups(c.m));
-  const size_t gel = c.m <= 64 ? 16 : 8;  // complex128 where the float64 gradient exists
-  L.gz = take((size_t)L.grad_chunk * m2 * gel);
-  L.gq = take((size_t)L.grad_probe_slots * m2 * gel);
+  L.gz = c.m == 256 ? Region{L.stack.off + (size_t)L.grad_chunk * m2 * 8, (size_t)L.grad_chunk * m2 * 8}
+                    : take(std::max((size_t)L.grad_chunk * 8, (size_t)L.grad_chunk64 * 16) * m2);
+  L.gq = take((size_t)L.grad_probe_slots * m2 * (c.m <= 64 ? 16 : 8));
   // scratch state for autotuning at init (only when asked for)
   const bool tune = wants_tuning(c);
   L.tune_obj = take(tune ? (size_t)c.n_rows * c.n_cols * 8 : 0);
@@ -1209,7 +1213,7 @@ emagpie_status emagpie_grad(emagpie_ctx ctx, const void* obj_dev, const void* pr
   g.dperm = ctx->dperm;
   g.pos = ctx->pos;
   g.n_pos = ctx->cfg.n_pos;
-  g.chunk = ctx->lay.grad_chunk;
+  g.chunk = f64 ? ctx->lay.grad_chunk64 : ctx->lay.grad_chunk;
   g.probe_slots = ctx->lay.grad_probe_slots;
   g.tw = f64 ? static_cast<const void*>(ctx->tw64) : static_cast<const void*>(ctx->tw32);
   g.gobj = grad_obj_dev;
