@@ -395,12 +395,13 @@ emagpie_status emagpie_misfit_noalloc(int32_t n_rows, int32_t n_cols, int32_t m,
 emagpie_status emagpie_debug_barrier(emagpie_ctx ctx, uint32_t spin_limit, uint32_t target_skew);
 
 /*
- * Test hook of the sequential sweep: with absent = 1 later sweeps of ctx wait at their
- * start for one workgroup more than is launched, so that every one of them gives the
- * sharing up and runs in one workgroup (same results, slower).  0 restores normal use;
- * EMAGPIE_E_ARG for other values.  Host only.
+ * Test hook of the sequential sweep, for what the device decides at its start: with
+ * absent = 1 later sweeps of ctx wait there for one workgroup more than is launched, so
+ * that every one of them gives the sharing up and runs in one workgroup; with apart = 1
+ * their workgroups exchange data as workgroups on several XCDs do, through memory.  Same
+ * results, slower.  0 and 0 restore normal use; EMAGPIE_E_ARG for values above 1.  Host only.
  */
-emagpie_status emagpie_debug_chain(emagpie_ctx ctx, uint32_t absent);
+emagpie_status emagpie_debug_chain(emagpie_ctx ctx, uint32_t absent, uint32_t apart);
 
 /*
  * Measured peaks for the roofline, on the caller's device buffer (bytes >=

@@ -286,6 +286,7 @@ struct emagpie_ctx_s {
   unsigned spin_limit = kDefaultSpinLimit;
   unsigned bar_skew = 0;  // extra arrivals awaited (fault injection; 0 in normal use)
   unsigned chain_absent = 0;  // workgroups a sequential sweep awaits that are not launched (likewise)
+  unsigned chain_apart = 0;   // its workgroups act as on several XCDs (likewise)
   std::string err;        // last failure of a call on this context
   // a context made by emagpie_init_many: its members and their group
   Many* many = nullptr;
@@ -369,7 +370,7 @@ emg::StepArgs base_args(emagpie_ctx c, void* obj, void* probe) {
 
 emg::ChainSync chain_sync(emagpie_ctx c) {
   return emg::ChainSync{reinterpret_cast<float2*>(c->ws + c->lay.chain.off), c->dev_err_dev,
-                        c->spin_limit, c->bar_skew, c->chain_absent};
+                        c->spin_limit, c->bar_skew, c->chain_absent, c->chain_apart};
 }
 
 // a (start, stop) event pair for timing category `cat`, or nulls when not timing
@@ -1651,11 +1652,12 @@ emagpie_status emagpie_debug_barrier(emagpie_ctx ctx, uint32_t spin_limit, uint3
   return EMAGPIE_OK;
 }
 
-emagpie_status emagpie_debug_chain(emagpie_ctx ctx, uint32_t absent) {
+emagpie_status emagpie_debug_chain(emagpie_ctx ctx, uint32_t absent, uint32_t apart) {
   CtxErrScope es_(ctx);
   EMG_OK(use_ctx(ctx));
-  if (absent > 1) return fail(EMAGPIE_E_ARG, "absent must be 0 or 1");
+  if (absent > 1 || apart > 1) return fail(EMAGPIE_E_ARG, "absent and apart must be 0 or 1");
   ctx->chain_absent = absent;
+  ctx->chain_apart = apart;
   return EMAGPIE_OK;
 }
 

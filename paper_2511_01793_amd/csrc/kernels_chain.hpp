@@ -486,7 +486,7 @@ __global__ __launch_bounds__((Chain<M, V>::NT)) void k_chain(StepArgs a, int n_s
   if (parties > 1) {
     const unsigned long long w = rolled;
     if (w & kRollOff) return;
-    shared_l2 = xcd < kDispatchXcds &&
+    shared_l2 = !y.apart && xcd < kDispatchXcds &&
                 (int)((w >> (kRollXcdBits * (xcd % kDispatchXcds))) & ((1 << kRollXcdBits) - 1)) == C::Workers;
     shared_l2 = __builtin_amdgcn_readfirstlane(shared_l2);
   }

@@ -105,6 +105,7 @@ struct ChainSync {
   unsigned spin_limit;  // polls of one wait before it gives up
   unsigned skew;        // added to the sequence numbers awaited (fault injection; 0 in normal use)
   unsigned absent;      // added to the workgroups awaited at the start (likewise)
+  unsigned apart;       // not 0: taken to be on several XCDs (likewise)
 };
 // Scratch layout, in 16-byte units: two copies of the tile and the updated window, m^2
 // each; the maxima of every wave; the counters; then (not cleared) the misfit terms of the

@@ -120,7 +120,7 @@ def lib() -> ctypes.CDLL:
         "emagpie_epoch_many": [vp, vp, vp, i64, vp, vp],
         "emagpie_many_member": [vp, i32, ctypes.POINTER(vp)],
         "emagpie_debug_barrier": [vp, ctypes.c_uint32, ctypes.c_uint32],
-        "emagpie_debug_chain": [vp, ctypes.c_uint32],
+        "emagpie_debug_chain": [vp, ctypes.c_uint32, ctypes.c_uint32],
         "emagpie_measure_peaks": [vp, sz, i32, vp, vp],
         "emagpie_misfit_noalloc": [i32, i32, i32, i32, vp, vp, vp, vp, vp, vp],
     }
@@ -307,10 +307,11 @@ class Reconstruction:
         the next call raises E_HIP."""
         _check(lib().emagpie_debug_barrier(self._ctx, int(spin_limit), int(target_skew)), self._ctx)
 
-    def debug_chain(self, absent: bool = False):
+    def debug_chain(self, absent: bool = False, apart: bool = False):
         """Test hook: with absent, later sequential sweeps wait for a workgroup that is not
-        launched, give the sharing up and run in one workgroup (same results)."""
-        _check(lib().emagpie_debug_chain(self._ctx, int(bool(absent))), self._ctx)
+        launched, give the sharing up and run in one workgroup; with apart, their workgroups
+        exchange data as on several XCDs (same results)."""
+        _check(lib().emagpie_debug_chain(self._ctx, int(bool(absent)), int(bool(apart))), self._ctx)
 
     @property
     def last_error(self) -> str:
